@@ -22,6 +22,16 @@ import workloads
 from paper_1511_08225_amd import autotune, slpic, warmstart
 
 DEV = "cuda"
+_STREAM: list = []
+
+
+def _stream():
+    """The program's side stream (graphs are captured on a side stream only):
+    one for all its runs, which follow one another."""
+    if not _STREAM:
+        _STREAM.append(torch.cuda.Stream())
+    return _STREAM[0]
+
 
 
 # --------------------------------------------------------------------------
@@ -170,7 +180,7 @@ def prepare(case: dict, seed: int) -> dict:
         return {"kind": kind, "net": net, "x": x, "t": t}
     cfgs = _configs(case, seed)
     prec, steps = case["precision"], case["steps"]
-    stream = torch.cuda.Stream()  # graphs are captured on a side stream only
+    stream = _stream()
     with torch.cuda.stream(stream):
         if kind == "sheath2d":
             sim = slpic.Sim2D(cfgs[0], case["ny"], precision=prec, sort_every=8, tile=8, graph_steps=8)
