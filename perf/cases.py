@@ -3,10 +3,11 @@
 Each case is one pass through public entry points.  The particle cases restart
 from a checkpoint of the run (the caller owns the workspace, so a device copy
 of it is the checkpoint), advance one block of steps, short enough that rounding
-noise does not grow into the result, and read the beta-weighted moments; the network cases are one prediction or one training step.  Shapes
-come from workloads.py and the benchmark (production sheath, its 10x variant,
-batched sweep, two-plate experiment, periodic boxes, 2D sheath, warm-start
-network) and from generic sizes between them.
+noise does not grow into the result, and read the beta-weighted moments; the
+network cases are one prediction or one training step.  Shapes come from
+workloads.py and the benchmark (production sheath, its 10x variant, batched
+sweep, two-plate experiment, periodic boxes, 2D sheath, warm-start network) and
+from generic sizes between them.
 
 Float-particle runs hand their moments on in single precision, the precision
 of their particles; double-particle runs in double.
@@ -31,8 +32,6 @@ def _stream():
     if not _STREAM:
         _STREAM.append(torch.cuda.Stream())
     return _STREAM[0]
-
-
 
 # --------------------------------------------------------------------------
 # the cases
@@ -128,14 +127,13 @@ def _configs(case: dict, seed: int) -> list[dict]:
 
 
 def _plates_state(cfg: dict, seed: int):
-    """A filled box between the plates: per species x (cells), v_x and
-    v_perp^2.  Ions enter through x = L at their thermal speed and fall to
-    the grounded plate; electrons follow the Boltzmann drop."""
+    """A filled box between the plates, about as many particles as the
+    experiment ends with: per species x (cells), v_x and v_perp^2.  Ions enter
+    through x = L with their thermal flux and fall to the grounded plate;
+    electrons follow the Boltzmann drop."""
     rng = np.random.default_rng(seed)
     nx, ppc = cfg["nx"], cfg["species"][0]["ppc"]
-    xi = np.arange(nx) / nx
-    phi = cfg["bias"] * np.tanh(6.0 * xi) / math.tanh(6.0)
-    drop = cfg["bias"] - phi
+    drop = cfg["bias"] * (1.0 - np.arange(nx) / nx)
     out = []
     for s, sp in enumerate(cfg["species"]):
         vt = math.sqrt(sp["temperature"] / sp["mass"])
@@ -143,9 +141,9 @@ def _plates_state(cfg: dict, seed: int):
             dens = np.exp(-drop)
             drift = np.zeros(nx)
         else:
-            v0 = math.sqrt(1.0 / sp["mass"])
+            v0 = math.sqrt(1.0 / sp["mass"])  # the ion sound speed
             drift = -np.sqrt(v0 * v0 + 2.0 * drop / sp["mass"])
-            dens = v0 / -drift
+            dens = vt / math.sqrt(2.0 * math.pi) / -drift
         cnt = (ppc * dens).astype(np.int64)
         cell = np.repeat(np.arange(nx), cnt)
         n = len(cell)
