@@ -364,7 +364,7 @@ struct Context {
     unsigned char* ws = nullptr;
     long long* btot = nullptr;
     int64_t steps_done = 0;
-    size_t field_lds = 0, source_field_lds = 0, sort_lds = 0, moments_lds = 0;
+    size_t field_lds = 0, source_field_lds = 0, sort_lds = 0;
     size_t scatter_lds = 0;  // four waves' packed per-key offsets
     // threads of the per-run source + field workgroup (fewer waves helped the
     // 100-cell plates step by ~5 % but slowed the 2048-cell sheath by 10-20 %)
@@ -455,16 +455,18 @@ int do_sort(Context* c, hipStream_t s) {
     });
 }
 
-// One leapfrog step of every run; `local_step` decides the sort.
-// The moments of every run added to their device windows (slpic_moments_sample).
-void sample_all(Context* c, hipStream_t s) {
-    if (prec(c) == SLPIC_F32)
-        launch_moments_f32(c->a, 0, (int)c->P.chunks.size(), 256, c->moments_lds, c->a.Macc, 1, s);
-    else
-        launch_moments_f64(c->a, 0, (int)c->P.chunks.size(), 256, c->moments_lds, c->a.Macc, 1, s);
-    launch_moments_sample_finish(c->a, 0, c->P.nruns, s);
+// The beta-weighted sums of nch chunks from ch0 added to out.
+void l_moments(Context* c, int ch0, int nch, double* out, int per_run, int phi_runs, hipStream_t s) {
+    if (prec(c) == SLPIC_F32) launch_moments_f32(c->a, ch0, nch, c->P.tun.chunk, out, per_run, phi_runs, s);
+    else launch_moments_f64(c->a, ch0, nch, c->P.tun.chunk, out, per_run, phi_runs, s);
 }
 
+// The moments of every run added to their device windows (slpic_moments_sample).
+void sample_all(Context* c, hipStream_t s) {
+    l_moments(c, 0, (int)c->P.chunks.size(), c->a.Macc, 1, c->P.nruns, s);
+}
+
+// One leapfrog step of every run; `local_step` decides the sort.
 int one_step(Context* c, int64_t local_step, hipStream_t s) {
     int rc;
     if (c->a.ninjb > 0 && (rc = timed(c, 1, s, [&] { l_wall_inject(c, s); }))) return rc;
@@ -630,8 +632,7 @@ int slpic_init(const slpic_run_config* runs, int32_t nruns, const slpic_tuning* 
     c->scatter_lds = (size_t)4 * ((c->P.max_nkeys + 1) / 2) * sizeof(uint32_t);
     c->source_field_lds = c->field_lds + (size_t)2 * c->P.max_src * 8;
 
-    c->moments_lds = (size_t)3 * c->P.max_nodes * 8;
-    if (c->sort_lds > 65536 || c->scatter_lds > 65536 || c->moments_lds > 65536 || c->source_field_lds > 65536) {
+    if (c->sort_lds > 65536 || c->scatter_lds > 65536 || c->source_field_lds > 65536) {
         delete c;
         return SLPIC_EINVAL;
     }
@@ -731,10 +732,7 @@ int slpic_moments(void* ctx, int32_t run, double* d_out, void* stream) {
     hipStream_t s = (hipStream_t)stream;
     const RunInfo& R = c->P.runs[run];
     launch_zero(d_out, (int64_t)7 * R.nodes, s);
-    if (prec(c) == SLPIC_F32)
-        launch_moments_f32(c->a, c->P.run_chunk0[run], c->P.run_nchunks[run], 256, c->moments_lds, d_out, 0, s);
-    else
-        launch_moments_f64(c->a, c->P.run_chunk0[run], c->P.run_nchunks[run], 256, c->moments_lds, d_out, 0, s);
+    l_moments(c, c->P.run_chunk0[run], c->P.run_nchunks[run], d_out, 0, 0, s);
     launch_moments_finish(c->a, run, d_out, s);
     return hipGetLastError() == hipSuccess ? SLPIC_OK : SLPIC_EHIP;
 }
@@ -746,11 +744,7 @@ int slpic_moments_sample(void* ctx, int32_t run, void* stream) {
     const int r0 = run < 0 ? 0 : run, nr = run < 0 ? c->P.nruns : 1;
     const int ch0 = c->P.run_chunk0[r0];
     const int nch = run < 0 ? (int)c->P.chunks.size() : c->P.run_nchunks[run];
-    if (prec(c) == SLPIC_F32)
-        launch_moments_f32(c->a, ch0, nch, 256, c->moments_lds, c->a.Macc, 1, s);
-    else
-        launch_moments_f64(c->a, ch0, nch, 256, c->moments_lds, c->a.Macc, 1, s);
-    launch_moments_sample_finish(c->a, r0, nr, s);
+    l_moments(c, ch0, nch, c->a.Macc, 1, nr, s);
     return hipGetLastError() == hipSuccess ? SLPIC_OK : SLPIC_EHIP;
 }
 

@@ -168,7 +168,11 @@ __global__ void k_zero_ints(int* p, int64_t n) {
 // Window means of the moment samples of one run (phi, then per species n,
 // Gamma_x, energy density, each node's sums over dV), optionally clearing
 // the window afterwards.  One workgroup.
-__global__ void k_moments_window(KArgs a, int run, double* out, int reset) {
+// A node's seven rows are read together: the launch is one workgroup's chain
+// of memory round trips (256 threads reading row after row: 16.5 us at 1000
+// nodes).
+constexpr int kMomWindowThreads = 1024;
+__global__ __launch_bounds__(kMomWindowThreads) void k_moments_window(KArgs a, int run, double* out, int reset) {
     const RunInfo& R = a.runs[run];
     RunState* st = a.state + run;
     const int nodes = R.nodes;
@@ -177,25 +181,20 @@ __global__ void k_moments_window(KArgs a, int run, double* out, int reset) {
     const double inv = ns > 0 ? 1.0 / (double)ns : 0.0;
     for (int j = threadIdx.x; j < nodes; j += blockDim.x) {
         const double dV = (j == 0 || j == nodes - 1) ? 0.5 * R.dx : R.dx;
-        out[j] = M[j] * inv;
-        for (int r = 1; r < 7; ++r) out[(int64_t)r * nodes + j] = M[(int64_t)r * nodes + j] * inv / dV;
+        double m[7];
+#pragma unroll
+        for (int r = 0; r < 7; ++r) m[r] = M[(int64_t)r * nodes + j];
+        out[j] = m[0] * inv;
+#pragma unroll
+        for (int r = 1; r < 7; ++r) out[(int64_t)r * nodes + j] = m[r] * inv / dV;
+        if (reset)
+#pragma unroll
+            for (int r = 0; r < 7; ++r) M[(int64_t)r * nodes + j] = 0.0;
     }
     if (reset) {
-        __syncthreads();
-        for (int j = threadIdx.x; j < 7 * nodes; j += blockDim.x) M[j] = 0.0;
+        __syncthreads();  // every thread has read the count
         if (threadIdx.x == 0) st->msamples = 0;
     }
-}
-
-// After the raw moment sums of a sample were added to the accumulators: add
-// phi and count the sample.  One workgroup per run.
-__global__ void k_moments_sample_finish(KArgs a, int run0) {
-    const int run = run0 + blockIdx.x;
-    const RunInfo& R = a.runs[run];
-    double* M = a.Macc + 7 * R.goff;
-    const double* phi = a.phi + R.goff;
-    for (int j = threadIdx.x; j < R.nodes; j += blockDim.x) M[j] += phi[j];
-    if (threadIdx.x == 0) a.state[run].msamples += 1;
 }
 
 __global__ void k_moments_finish(KArgs a, int run, double* out) {
@@ -247,10 +246,7 @@ void launch_zero(double* p, int64_t n, hipStream_t s) {
     hipLaunchKernelGGL(k_zero, dim3((unsigned)blocks), dim3(256), 0, s, p, n);
 }
 void launch_moments_window(const KArgs& a, int run, double* out, int reset, hipStream_t s) {
-    hipLaunchKernelGGL(k_moments_window, dim3(1), dim3(256), 0, s, a, run, out, reset);
-}
-void launch_moments_sample_finish(const KArgs& a, int run0, int nruns, hipStream_t s) {
-    hipLaunchKernelGGL(k_moments_sample_finish, dim3(nruns), dim3(256), 0, s, a, run0);
+    hipLaunchKernelGGL(k_moments_window, dim3(1), dim3(kMomWindowThreads), 0, s, a, run, out, reset);
 }
 void launch_moments_finish(const KArgs& a, int run, double* out, hipStream_t s) {
     hipLaunchKernelGGL(k_moments_finish, dim3(8), dim3(256), 0, s, a, run, out);

@@ -18,8 +18,8 @@ namespace slpic {
     void launch_source_field_##sfx(const KArgs& a, int nruns, int threads, size_t lds, hipStream_t s); \
     void launch_wall_inject_##sfx(const KArgs& a, hipStream_t s);                                      \
     void launch_limit_##sfx(const KArgs& a, const LimitArgs& L, int nchunks, int scatter, hipStream_t s); \
-    void launch_moments_##sfx(const KArgs& a, int chunk0, int nchunks, int block, size_t lds,          \
-                              double* out, int per_run, hipStream_t s);                                \
+    void launch_moments_##sfx(const KArgs& a, int chunk0, int nchunks, int chunk, double* out,         \
+                              int per_run, int phi_runs, hipStream_t s);                               \
     void launch_sort_hist_##sfx(const KArgs& a, int ntiles, int block, size_t lds, hipStream_t s);     \
     void launch_sort_scatter_##sfx(const KArgs& a, int ntiles, int block, size_t lds, hipStream_t s);
 
@@ -41,6 +41,5 @@ void launch_zero_ints(int* p, int64_t n, hipStream_t s);
 void launch_limit_finish(const KArgs& a, int nruns, int64_t total_slots, const long long* btot, hipStream_t s);
 void launch_moments_finish(const KArgs& a, int run, double* out, hipStream_t s);
 void launch_moments_window(const KArgs& a, int run, double* out, int reset, hipStream_t s);
-void launch_moments_sample_finish(const KArgs& a, int run0, int nruns, hipStream_t s);
 
 }  // namespace slpic

@@ -18,8 +18,7 @@ constexpr int kLimitMaxCopies = 255;  // copies of one g-particle when the speed
 constexpr int kGeomSheath = 0;        // symmetry plane at 0, grounded wall at L
 constexpr int kGeomPlates = 1;        // conducting plates at 0 and L (bias)
 constexpr int kGeomPeriodic = 2;      // periodic box, no walls, no source
-// cells of a 1D run: a moments workgroup keeps 3 FP64 rows of nodes in its
-// 64 KiB of LDS (3 * 8 * 2730 bytes)
+// cells of a 1D run (the interface's limit)
 constexpr int kMaxCells = 2729;
 constexpr int kFieldThreads = 1024;   // field solve: threads of the per-run workgroup
 constexpr int kFieldTmp = 32;         // field solve: LDS doubles after the node row (two scans' wave totals)
