@@ -444,8 +444,8 @@ int slpic2d_moments(void* ctx, double* d_out, void* stream) {
     hipStream_t s = (hipStream_t)stream;
     const Run2D& R = c->P.R;
     launch2d_fill(d_out, 7 * R.nodes, s);
-    if (f32(c)) launch2d_moments_f32(c->a, std::max(R.cap[0], R.cap[1]), d_out, s);
-    else launch2d_moments_f64(c->a, std::max(R.cap[0], R.cap[1]), d_out, s);
+    if (f32(c)) launch2d_moments_f32(c->a, R.nkeys, R.win, std::max(R.cap[0], R.cap[1]), d_out, s);
+    else launch2d_moments_f64(c->a, R.nkeys, R.win, std::max(R.cap[0], R.cap[1]), d_out, s);
     launch2d_moments_finish(c->a, R.nodes, d_out, s);
     return hipGetLastError() == hipSuccess ? SLPIC_OK : SLPIC_EHIP;
 }
