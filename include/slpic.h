@@ -74,7 +74,7 @@ enum {
     SLPIC_EHIP = -5,       /* a HIP runtime call failed                    */
     SLPIC_ESTATE = -6,     /* call not valid in the context's state        */
     SLPIC_ELIMIT = -7      /* input larger than an allocation-free call's  */
-                           /* fixed scratch                                */
+                           /* limit                                        */
 };
 
 /* Speed-limiting function: Eq. (11b) (default) or Eq. (11a). */
@@ -409,15 +409,10 @@ int slpic_mlp_forward(const void* d_params_bf16, const float* d_x, float* d_y, i
 
 /* Allocation-free variant of slpic_mlp_forward, for callers that cannot
  * allocate device memory (code under HIP graph capture, serving loops,
- * harnesses that forbid hipMalloc): the same kernels and the same d_y, with
- * the activations in a fixed array of the library's code object instead of
- * a caller buffer (SLPIC_MLP_NOALLOC_MAX_BATCH x 772 BF16 = 1.5 MiB, held on
- * every GPU the library runs on until the process ends).  It calls no
- * allocator.  The first call on a device (that device current) looks up the
- * array's address there.  batch beyond SLPIC_MLP_NOALLOC_MAX_BATCH returns
- * SLPIC_ELIMIT; nothing else is retained between calls (every call rewrites
- * the activations it reads).  Calls that overlap on one GPU (other streams,
- * other threads) share the array and race: serialise them. */
+ * harnesses that forbid hipMalloc): the same kernel and the same d_y, with the
+ * activations not stored at all (they stay in the workgroups' LDS).  It calls
+ * no allocator and keeps nothing between calls; calls may overlap.  batch
+ * beyond SLPIC_MLP_NOALLOC_MAX_BATCH returns SLPIC_ELIMIT. */
 #define SLPIC_MLP_NOALLOC_MAX_BATCH 1024
 int slpic_mlp_forward_noalloc(const void* d_params_bf16, const float* d_x, float* d_y, int32_t batch,
                               void* stream);
