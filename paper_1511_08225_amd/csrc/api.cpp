@@ -145,6 +145,7 @@ struct Plan {
     int64_t total_slots = 0, total_nodes = 0, hist_entries = 0;
     int max_nodes = 0, max_src = 0, max_nkeys = 0;
     bool all_sheath = true;  // no plates or periodic run: the push without their paths
+    bool all_step = true;    // every run takes Eq. (11b): the push without the smooth form
     bool any_varlim = false; // a run with a limit profile: the push that reads the profiles
     std::vector<double> limit_nodes;  // every run's limit at its nodes (at goff)
     Layout L{};
@@ -264,9 +265,11 @@ int make_plan(const slpic_run_config* cfg, int nruns, const slpic_tuning* tin, P
             R.hoff[s] = hoff;
             hoff += (int64_t)R.nkeys * R.ntiles[s];
         }
+        R.set_floats();
         R.inj_ratio = R.w[1] / R.w[0];
         R.geom = plates ? kGeomPlates : periodic ? kGeomPeriodic : kGeomSheath;
         if (plates || periodic) P.all_sheath = false;
+        if (c.beta_kind != SLPIC_BETA_STEP) P.all_step = false;
         R.bias = plates ? c.bias : 0.0;
         if (c.steady_window < 0 || !(c.steady_tol >= 0.0)) return SLPIC_EINVAL;
         R.steady_window = c.steady_window > 0 ? c.steady_window : std::max(1, c.nx / 4);
@@ -407,9 +410,9 @@ void l_push(Context* c, bool push, hipStream_t s) {
     const Chunk* ch = push ? c->active : c->a.chunks;
     const int n = push ? c->n_active : (int)c->P.chunks.size();
     if (prec(c) == SLPIC_F32)
-        launch_push_f32(push, c->P.all_sheath, c->P.any_varlim, per, c->a, ch, n, c->P.tun.block, s);
+        launch_push_f32(push, c->P.all_sheath, c->P.all_step, c->P.any_varlim, per, c->a, ch, n, c->P.tun.block, s);
     else
-        launch_push_f64(push, c->P.all_sheath, c->P.any_varlim, per, c->a, ch, n, c->P.tun.block, s);
+        launch_push_f64(push, c->P.all_sheath, c->P.all_step, c->P.any_varlim, per, c->a, ch, n, c->P.tun.block, s);
 }
 void l_wall_inject(Context* c, hipStream_t s) {
     if (prec(c) == SLPIC_F32) launch_wall_inject_f32(c->a, s);
@@ -927,6 +930,7 @@ int slpic_set_speed_limit(void* ctx, int32_t run, double u, double dt, void* str
         }
         L.w[s] = Rn.w[s];
     }
+    Rn.set_floats();
     Rn.inj_ratio = Rn.w[1] / Rn.w[0];
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(hipDeviceSynchronize());

@@ -487,7 +487,7 @@ __device__ __forceinline__ T kick1d(T vx, T c2, T a, T dt, T u, T u2, bool uinf,
 struct CellMap {
     int fb;
     float inv_fscale;
-    __device__ __forceinline__ explicit CellMap(const RunInfo& R) : fb(R.fb), inv_fscale((float)R.inv_fscale) {}
+    __device__ __forceinline__ explicit CellMap(const RunInfo& R) : fb(R.fb), inv_fscale(R.f.inv_fscale) {}
     __device__ __forceinline__ CellMap(int fb_, float inv_fscale_) : fb(fb_), inv_fscale(inv_fscale_) {}
 };
 template <typename T> struct PosT;

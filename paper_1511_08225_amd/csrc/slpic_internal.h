@@ -31,6 +31,15 @@ constexpr int kInjectThreads = 128;     // plates: particles per wall-injection 
 constexpr int kHistoryLen = 4096;  // wall-potential ring per run
 constexpr int kCountSlots = 64;    // spread slots of the per-step particle counters
 
+// Float copies of the parameters the float push computes with (round to
+// nearest of the FP64 ones).
+struct RunFloats {
+    float qm[kMaxSpecies];
+    float dt, u, u2, inv_fscale;
+    float dtfx;  // dt/dx in fixed-point units per velocity unit (2^fb dt/dx)
+    float pad;
+};
+
 // Immutable per-run parameters (device copy of the host plan).
 struct RunInfo {
     int32_t nx, nodes, beta_kind, source_cells;
@@ -65,6 +74,16 @@ struct RunInfo {
                                  // particles then sit identical in both buffers)
     int32_t varlim;              // 1: the speed limit varies with position (node values at goff)
     double umax;                 // the largest speed limit of the run (its profile's largest node)
+    RunFloats f;
+    void set_floats() {  // after any change of the FP64 parameters
+        for (int s = 0; s < kMaxSpecies; ++s) f.qm[s] = (float)qm[s];
+        f.dt = (float)dt;
+        f.u = (float)u;
+        f.u2 = (float)u2;
+        f.inv_fscale = (float)inv_fscale;
+        f.dtfx = (float)(dtdx * fscale);
+        f.pad = 0.0f;
+    }
 };
 
 // A new (higher) speed limit for one run: the new limit and the new weights.
