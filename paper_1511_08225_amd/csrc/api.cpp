@@ -328,7 +328,7 @@ int make_plan(const slpic_run_config* cfg, int nruns, const slpic_tuning* tin, P
     L.state = take(sizeof(RunState) * nruns);
     L.chunks = take(sizeof(Chunk) * P.chunks.size());
     L.tiles = take(sizeof(Tile) * P.tiles.size());
-    L.cur = take(sizeof(int));
+    L.cur = take(2 * sizeof(int));  // the current buffer; workgroups of a scatter that have ended
     for (int b = 0; b < 2; ++b) {
         L.x[b] = take(psz * P.total_slots);
         L.vx[b] = take(vsz * P.total_slots);
@@ -445,16 +445,22 @@ int timed(Context* c, int k, hipStream_t s, F&& f) {
 
 int do_sort(Context* c, hipStream_t s) {
     const int nt = (int)c->P.tiles.size();
+    // the (key, tile) counts: a small table is written whole by its tiles (256K
+    // 4-byte stores cost less than the launch that zeroes it, 4.5 us), a large
+    // one starts at zero
+    const int64_t entries = c->P.hist_entries;
+    const int whole = entries <= (int64_t)1 << 18;
     return timed(c, 3, s, [&] {
-        // the (key, tile) counts start at zero: a tile writes only the keys it holds
-        launch_zero_ints(c->a.hist, c->P.hist_entries, s);
-        if (prec(c) == SLPIC_F32) launch_sort_hist_f32(c->a, nt, 256, c->sort_lds, s);
-        else launch_sort_hist_f64(c->a, nt, 256, c->sort_lds, s);
+        if (!whole) launch_zero_ints(c->a.hist, entries, s);
+        if (prec(c) == SLPIC_F32) launch_sort_hist_f32(c->a, nt, 256, c->sort_lds, whole, s);
+        else launch_sort_hist_f64(c->a, nt, 256, c->sort_lds, whole, s);
         // both sort kernels run four waves per tile: scatter_lds is sized for them
-        launch_sort_scan(c->a, c->P.hist_entries, c->btot, s);
-        if (prec(c) == SLPIC_F32) launch_sort_scatter_f32(c->a, nt, 256, c->scatter_lds, s);
-        else launch_sort_scatter_f64(c->a, nt, 256, c->scatter_lds, s);
-        launch_sort_finish(c->a, c->P.nruns, c->P.hist_entries, c->btot, s);
+        launch_sort_scan(c->a, entries, c->btot, s);
+        const long long* total = c->btot + scan_blocks(entries);
+        if (prec(c) == SLPIC_F32)
+            launch_sort_scatter_f32(c->a, nt, 256, c->scatter_lds, c->P.nruns, entries, total, s);
+        else
+            launch_sort_scatter_f64(c->a, nt, 256, c->scatter_lds, c->P.nruns, entries, total, s);
     });
 }
 

@@ -11,7 +11,7 @@ namespace slpic {
 
 __global__ void k_init_state(KArgs a, int nruns) {
     int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r == 0) *a.cur = 0;
+    if (r == 0) a.cur[0] = a.cur[1] = 0;
     if (r >= nruns) return;
     RunState* st = a.state + r;
     const RunInfo& R = a.runs[r];
@@ -49,12 +49,15 @@ __global__ __launch_bounds__(kFieldThreads) void k_field(KArgs a, int advance) {
 }
 
 // Exclusive scan of the sort histogram, in place, over all (run, species)
-// segments at once: block sums, a scan of the block sums, then each block
-// rescanned with its offset.  A segment's first entry is then its base and
-// the next segment's first entry (or the grand total) its end.
+// segments at once: block sums, then each block rescanned, its offset the sum
+// of the blocks before it, which it adds up itself (one read per thread up to
+// 1024 blocks; a launch between the two that scans the block sums costs 4.5
+// us, as much as either).  A table of one block needs no block sums.  A
+// segment's first entry is then its base and the next segment's first entry
+// (or the grand total) its end.
 constexpr int kScanBlock = 8192;
 
-__global__ void k_scan_blocks(int* h, int64_t n, long long* btot) {
+__global__ void k_scan_blocks(const int* h, int64_t n, long long* btot) {
     __shared__ long long tmp[17];
     const int64_t b0 = (int64_t)blockIdx.x * kScanBlock;
     const int64_t b1 = min(b0 + kScanBlock, n);
@@ -65,29 +68,15 @@ __global__ void k_scan_blocks(int* h, int64_t n, long long* btot) {
     if (threadIdx.x == blockDim.x - 1) btot[blockIdx.x] = ex + loc;
 }
 
-__global__ void k_scan_top(long long* btot, int nblk) {
-    __shared__ long long tmp[17];
-    const int per = (nblk + blockDim.x - 1) / blockDim.x;
-    const int j0 = threadIdx.x * per, j1 = min(j0 + per, nblk);
-    long long loc = 0;
-    for (int j = j0; j < j1; ++j) loc += btot[j];
-    long long run = block_scan<long long>(loc, tmp, false);
-    for (int j = j0; j < j1; ++j) {
-        long long c = btot[j];
-        btot[j] = run;
-        run += c;
-    }
-    if (threadIdx.x == blockDim.x - 1) btot[nblk] = run;  // grand total
-}
-
 // Launched with kScanThreads threads: each holds kScanPer consecutive
 // entries in registers (two 16-byte loads and stores where all are in range;
-// h is 16-byte aligned).
+// h is 16-byte aligned).  The last block writes the grand total to
+// btot[gridDim.x].
 constexpr int kScanThreads = 1024;
 constexpr int kScanPer = kScanBlock / kScanThreads;
 static_assert(kScanPer == 8, "two int4 per thread");
-__global__ __launch_bounds__(kScanThreads) void k_scan_apply(int* h, int64_t n, const long long* btot) {
-    __shared__ long long tmp[17];
+__global__ __launch_bounds__(kScanThreads) void k_scan_apply(int* h, int64_t n, long long* btot) {
+    __shared__ long long tmp[17], before[1];
     const int64_t j0 = (int64_t)blockIdx.x * kScanBlock + (int64_t)threadIdx.x * kScanPer;
     const bool full = j0 + kScanPer <= n;
     int v[kScanPer];
@@ -99,10 +88,15 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(int* h, int64_t n, 
 #pragma unroll
         for (int i = 0; i < kScanPer; ++i) v[i] = j0 + i < n ? h[j0 + i] : 0;
     }
+    long long prev = 0;
+    for (int j = threadIdx.x; j < (int)blockIdx.x; j += kScanThreads) prev += btot[j];
+    const long long pex = block_scan<long long>(prev, tmp, false);
+    if (threadIdx.x == kScanThreads - 1) before[0] = pex + prev;
     long long loc = 0;
 #pragma unroll
     for (int i = 0; i < kScanPer; ++i) loc += v[i];
-    long long run = btot[blockIdx.x] + block_scan<long long>(loc, tmp, false);
+    long long run = block_scan<long long>(loc, tmp, false);
+    run += before[0];  // written before the scan's barriers
     int o[kScanPer];
 #pragma unroll
     for (int i = 0; i < kScanPer; ++i) {
@@ -117,22 +111,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(int* h, int64_t n, 
         for (int i = 0; i < kScanPer; ++i)
             if (j0 + i < n) h[j0 + i] = o[i];
     }
-}
-
-// After the scatter: the sorted buffer becomes current and holds exactly the
-// live particles of each (run, species).
-__global__ void k_sort_finish(KArgs a, int nruns, int64_t hist_entries, const long long* btot, int nblk) {
-    int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r == 0) *a.cur ^= 1;
-    if (r >= nruns) return;
-    const RunInfo& R = a.runs[r];
-    if (R.pruned) return;  // not sorted: its counts stand
-    for (int s = 0; s < kMaxSpecies; ++s) {
-        const int64_t e = R.hoff[s] + (int64_t)R.nkeys * R.ntiles[s];
-        const long long base = a.hist[R.hoff[s]];
-        const long long end = e < hist_entries ? (long long)a.hist[e] : btot[nblk];
-        a.state[r].nslots[s] = end - base;
-    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kScanThreads - 1) btot[gridDim.x] = run;
 }
 
 // After a speed-limit resampling: every (run, species) segment's new count
@@ -217,17 +196,11 @@ void launch_field(const KArgs& a, int nruns, int advance, size_t lds, hipStream_
 int scan_blocks(int64_t n) { return (int)((n + kScanBlock - 1) / kScanBlock); }
 void launch_scan_ints(int* h, int64_t n, long long* btot, hipStream_t s) {
     const int nblk = scan_blocks(n);
-    hipLaunchKernelGGL(k_scan_blocks, dim3(nblk), dim3(1024), 0, s, h, n, btot);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, btot, nblk);
-    hipLaunchKernelGGL(k_scan_apply, dim3(nblk), dim3(kScanThreads), 0, s, h, n, (const long long*)btot);
+    if (nblk > 1) hipLaunchKernelGGL(k_scan_blocks, dim3(nblk), dim3(1024), 0, s, (const int*)h, n, btot);
+    hipLaunchKernelGGL(k_scan_apply, dim3(nblk), dim3(kScanThreads), 0, s, h, n, btot);
 }
 void launch_sort_scan(const KArgs& a, int64_t hist_entries, long long* btot, hipStream_t s) {
     launch_scan_ints(a.hist, hist_entries, btot, s);
-}
-void launch_sort_finish(const KArgs& a, int nruns, int64_t hist_entries, const long long* btot,
-                        hipStream_t s) {
-    hipLaunchKernelGGL(k_sort_finish, dim3((nruns + 255) / 256), dim3(256), 0, s, a, nruns, hist_entries,
-                       btot, scan_blocks(hist_entries));
 }
 void launch_limit_finish(const KArgs& a, int nruns, int64_t total_slots, const long long* btot, hipStream_t s) {
     hipLaunchKernelGGL(k_limit_finish, dim3((nruns + 255) / 256), dim3(256), 0, s, a, nruns, total_slots, btot,

@@ -20,8 +20,10 @@ namespace slpic {
     void launch_limit_##sfx(const KArgs& a, const LimitArgs& L, int nchunks, int scatter, hipStream_t s); \
     void launch_moments_##sfx(const KArgs& a, int chunk0, int nchunks, int chunk, double* out,         \
                               int per_run, int phi_runs, hipStream_t s);                               \
-    void launch_sort_hist_##sfx(const KArgs& a, int ntiles, int block, size_t lds, hipStream_t s);     \
-    void launch_sort_scatter_##sfx(const KArgs& a, int ntiles, int block, size_t lds, hipStream_t s);
+    void launch_sort_hist_##sfx(const KArgs& a, int ntiles, int block, size_t lds, int whole,          \
+                                hipStream_t s);                                                        \
+    void launch_sort_scatter_##sfx(const KArgs& a, int ntiles, int block, size_t lds, int nruns,       \
+                                   int64_t hist_entries, const long long* total, hipStream_t s);
 
 SLPIC_DECLARE_LAUNCHERS(f32)
 SLPIC_DECLARE_LAUNCHERS(f64)
@@ -34,8 +36,6 @@ int scan_blocks(int64_t hist_entries);
 void launch_sort_scan(const KArgs& a, int64_t hist_entries, long long* btot, hipStream_t s);
 // exclusive scan of n ints in place; btot[scan_blocks(n)] receives the total
 void launch_scan_ints(int* h, int64_t n, long long* btot, hipStream_t s);
-void launch_sort_finish(const KArgs& a, int nruns, int64_t hist_entries, const long long* btot,
-                        hipStream_t s);
 void launch_zero(double* p, int64_t n, hipStream_t s);
 void launch_zero_ints(int* p, int64_t n, hipStream_t s);
 void launch_limit_finish(const KArgs& a, int nruns, int64_t total_slots, const long long* btot, hipStream_t s);
