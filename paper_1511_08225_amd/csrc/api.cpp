@@ -328,7 +328,7 @@ int make_plan(const slpic_run_config* cfg, int nruns, const slpic_tuning* tin, P
     L.state = take(sizeof(RunState) * nruns);
     L.chunks = take(sizeof(Chunk) * P.chunks.size());
     L.tiles = take(sizeof(Tile) * P.tiles.size());
-    L.cur = take(2 * sizeof(int));  // the current buffer; workgroups of a scatter that have ended
+    L.cur = take(sizeof(int));
     for (int b = 0; b < 2; ++b) {
         L.x[b] = take(psz * P.total_slots);
         L.vx[b] = take(vsz * P.total_slots);
@@ -445,9 +445,11 @@ int timed(Context* c, int k, hipStream_t s, F&& f) {
 
 int do_sort(Context* c, hipStream_t s) {
     const int nt = (int)c->P.tiles.size();
-    // the (key, tile) counts: a small table is written whole by its tiles (256K
-    // 4-byte stores cost less than the launch that zeroes it, 4.5 us), a large
-    // one starts at zero
+    // the (key, tile) counts: a small table is written whole by its tiles, which
+    // saves the launch that zeroes it, a large one starts at zero (a sort with the
+    // table written whole and zeroed: 19.0 and 20.8 us at 1280 entries, 25.4 and
+    // 26.4 at 116K, 26.8 and 27.2 at 246K, 27.8 and 27.8 at 307K, 29.8 and 28.6 at
+    // 461K, 112 and 69 at 6.1M)
     const int64_t entries = c->P.hist_entries;
     const int whole = entries <= (int64_t)1 << 18;
     return timed(c, 3, s, [&] {
@@ -456,11 +458,9 @@ int do_sort(Context* c, hipStream_t s) {
         else launch_sort_hist_f64(c->a, nt, 256, c->sort_lds, whole, s);
         // both sort kernels run four waves per tile: scatter_lds is sized for them
         launch_sort_scan(c->a, entries, c->btot, s);
-        const long long* total = c->btot + scan_blocks(entries);
-        if (prec(c) == SLPIC_F32)
-            launch_sort_scatter_f32(c->a, nt, 256, c->scatter_lds, c->P.nruns, entries, total, s);
-        else
-            launch_sort_scatter_f64(c->a, nt, 256, c->scatter_lds, c->P.nruns, entries, total, s);
+        if (prec(c) == SLPIC_F32) launch_sort_scatter_f32(c->a, nt, 256, c->scatter_lds, s);
+        else launch_sort_scatter_f64(c->a, nt, 256, c->scatter_lds, s);
+        launch_sort_finish(c->a, c->P.nruns, entries, c->btot, s);
     });
 }
 

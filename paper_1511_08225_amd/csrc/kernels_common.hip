@@ -11,7 +11,7 @@ namespace slpic {
 
 __global__ void k_init_state(KArgs a, int nruns) {
     int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r == 0) a.cur[0] = a.cur[1] = 0;
+    if (r == 0) *a.cur = 0;
     if (r >= nruns) return;
     RunState* st = a.state + r;
     const RunInfo& R = a.runs[r];
@@ -51,8 +51,7 @@ __global__ __launch_bounds__(kFieldThreads) void k_field(KArgs a, int advance) {
 // Exclusive scan of the sort histogram, in place, over all (run, species)
 // segments at once: block sums, then each block rescanned, its offset the sum
 // of the blocks before it, which it adds up itself (one read per thread up to
-// 1024 blocks; a launch between the two that scans the block sums costs 4.5
-// us, as much as either).  A table of one block needs no block sums.  A
+// 1024 blocks), without a launch between the two that scans the block sums.  A table of one block needs no block sums.  A
 // segment's first entry is then its base and the next segment's first entry
 // (or the grand total) its end.
 constexpr int kScanBlock = 8192;
@@ -112,6 +111,22 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(int* h, int64_t n, 
             if (j0 + i < n) h[j0 + i] = o[i];
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kScanThreads - 1) btot[gridDim.x] = run;
+}
+
+// After the scatter: the sorted buffer becomes current and holds exactly the
+// live particles of each (run, species).
+__global__ void k_sort_finish(KArgs a, int nruns, int64_t hist_entries, const long long* btot, int nblk) {
+    int r = blockIdx.x * blockDim.x + threadIdx.x;
+    if (r == 0) *a.cur ^= 1;
+    if (r >= nruns) return;
+    const RunInfo& R = a.runs[r];
+    if (R.pruned) return;  // not sorted: its counts stand
+    for (int s = 0; s < kMaxSpecies; ++s) {
+        const int64_t e = R.hoff[s] + (int64_t)R.nkeys * R.ntiles[s];
+        const long long base = a.hist[R.hoff[s]];
+        const long long end = e < hist_entries ? (long long)a.hist[e] : btot[nblk];
+        a.state[r].nslots[s] = end - base;
+    }
 }
 
 // After a speed-limit resampling: every (run, species) segment's new count
@@ -201,6 +216,11 @@ void launch_scan_ints(int* h, int64_t n, long long* btot, hipStream_t s) {
 }
 void launch_sort_scan(const KArgs& a, int64_t hist_entries, long long* btot, hipStream_t s) {
     launch_scan_ints(a.hist, hist_entries, btot, s);
+}
+void launch_sort_finish(const KArgs& a, int nruns, int64_t hist_entries, const long long* btot,
+                        hipStream_t s) {
+    hipLaunchKernelGGL(k_sort_finish, dim3((nruns + 255) / 256), dim3(256), 0, s, a, nruns, hist_entries,
+                       btot, scan_blocks(hist_entries));
 }
 void launch_limit_finish(const KArgs& a, int nruns, int64_t total_slots, const long long* btot, hipStream_t s) {
     hipLaunchKernelGGL(k_limit_finish, dim3((nruns + 255) / 256), dim3(256), 0, s, a, nruns, total_slots, btot,

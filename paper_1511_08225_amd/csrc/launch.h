@@ -22,8 +22,7 @@ namespace slpic {
                               int per_run, int phi_runs, hipStream_t s);                               \
     void launch_sort_hist_##sfx(const KArgs& a, int ntiles, int block, size_t lds, int whole,          \
                                 hipStream_t s);                                                        \
-    void launch_sort_scatter_##sfx(const KArgs& a, int ntiles, int block, size_t lds, int nruns,       \
-                                   int64_t hist_entries, const long long* total, hipStream_t s);
+    void launch_sort_scatter_##sfx(const KArgs& a, int ntiles, int block, size_t lds, hipStream_t s);
 
 SLPIC_DECLARE_LAUNCHERS(f32)
 SLPIC_DECLARE_LAUNCHERS(f64)
@@ -33,6 +32,8 @@ SLPIC_DECLARE_LAUNCHERS(f64)
 void launch_init_state(const KArgs& a, int nruns, hipStream_t s);
 void launch_field(const KArgs& a, int nruns, int advance, size_t lds, hipStream_t s);
 int scan_blocks(int64_t hist_entries);
+void launch_sort_finish(const KArgs& a, int nruns, int64_t hist_entries, const long long* btot,
+                        hipStream_t s);
 void launch_sort_scan(const KArgs& a, int64_t hist_entries, long long* btot, hipStream_t s);
 // exclusive scan of n ints in place; btot[scan_blocks(n)] receives the total
 void launch_scan_ints(int* h, int64_t n, long long* btot, hipStream_t s);

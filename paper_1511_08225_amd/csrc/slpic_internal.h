@@ -158,8 +158,7 @@ struct KArgs {
     const Chunk* chunks;
     const Tile* tiles;
     Bufs bufs;
-    int* cur;             // [0]: which of the two particle buffers is current; [1]: sort scatter
-                          // workgroups that have ended (0 between sorts)
+    int* cur;             // which of the two particle buffers is current
     double* E;            // node field, per run at goff
     float* E32;           // float copy of the node field (float particles gather it)
     double* phi;          // node potential

@@ -1,6 +1,5 @@
 """The cell sort over the sizes of its (key, tile) table: one scan block or
-several, written whole by its tiles or zeroed first, one key or thousands, and
-run sets whose requested tiles and push chunks are larger than they fill.  The
+several, written whole by its tiles or zeroed first, one key or thousands.  The
 sorted particles are NumPy's stable argsort of the unsorted ones, bit for bit,
 and two sorts in a row leave them alone."""
 import numpy as np
@@ -19,7 +18,7 @@ pytestmark = pytest.mark.gpu
     (256, 120, 1, 1024, "f64"),    # 45 tiles: 23040 entries, three scan blocks
     (1000, 80, 1, 1024, "f32"),    # 118 tiles: 236000 entries, the table written whole
     (1200, 80, 1, 1024, "f32"),    # 141 tiles: 338400 entries, the table zeroed first
-    (2729, 30, 7, 32768, "f32"),   # the requested tile larger than a species
+    (2729, 30, 7, 32768, "f32"),   # the largest tile: 4 per species at most
 ])
 def test_sort_is_stable_over_table_sizes(gpu_lib, nx, ppc, bucket, tile, prec):
     print_case(f"sort table nx={nx} ppc={ppc} bucket={bucket} tile={tile} {prec}")
