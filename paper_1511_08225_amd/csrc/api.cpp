@@ -151,6 +151,32 @@ struct Plan {
     Layout L{};
 };
 
+// The push chunk and the sort tile are upper bounds: a run set too small to
+// fill the chip with them takes smaller ones.  A wavefront works through its
+// P particles per lane one after another, so with fewer than about
+// kMinPushWaves wavefronts (two per SIMD) the launch takes as long as one of
+// them: whole FP32 steps of 517k particles take 30.3, 24.0, 24.1 us at 512,
+// 256, 128 slots per wavefront, of 12.8k 27.7, 20.5, 16.5 and 14.4 at 64;
+// FP64 ones of 400k 29.2, 25.3, 28.5 at 256, 128, 64.  (Plates runs count
+// their slots, of which an eighth fills: their many waves on few nodes contend
+// for the charge, 29.3, 33.6, 46.0 us a step at 256, 128, 64.)  Sort tiles
+// likewise: below kMinSortTiles workgroups the scatter takes as long as one
+// tile's serial rows: the FP32 steps above take 30.4, 25.1, 24.0, 24.0 us with
+// 16384, 4096, 2048 and 1024 slots per tile, and 512 slots, whose table is
+// larger, are slower.  Launches and the sort's table go by the slots, so a
+// run with more than four per particle loaded counts a quarter of its slots:
+// empty wavefronts cost 0.2 us per 1000.
+void fit_launch(const slpic_run_config* cfg, int nruns, slpic_tuning& t) {
+    constexpr double kMinPushWaves = 2048.0, kMinSortTiles = 512.0;
+    constexpr int kMinSortTile = 1024;
+    double load = 0.0;
+    for (int r = 0; r < nruns; ++r)
+        for (int s = 0; s < 2; ++s)
+            load += (double)cfg[r].nx * (double)cfg[r].species[s].ppc * std::max(1.0, cfg[r].capacity_factor / 4.0);
+    while (t.chunk > 64 && load < kMinPushWaves * t.chunk) t.chunk /= 2;
+    while (t.sort_tile >= 2 * kMinSortTile && load < kMinSortTiles * t.sort_tile) t.sort_tile /= 2;
+}
+
 int make_plan(const slpic_run_config* cfg, int nruns, const slpic_tuning* tin, Plan& P) {
     if (!cfg || nruns < 1) return SLPIC_EINVAL;
     slpic_tuning t{};
@@ -172,6 +198,7 @@ int make_plan(const slpic_run_config* cfg, int nruns, const slpic_tuning* tin, P
     }
     if (t.sort_every > 0 && t.graph_steps > 0 && t.graph_steps % t.sort_every)
         t.graph_steps = (t.graph_steps / t.sort_every + 1) * t.sort_every;
+    fit_launch(cfg, nruns, t);
     P.tun = t;
     P.nruns = nruns;
     P.runs.assign(nruns, RunInfo{});

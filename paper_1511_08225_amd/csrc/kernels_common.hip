@@ -49,11 +49,12 @@ __global__ __launch_bounds__(kFieldThreads) void k_field(KArgs a, int advance) {
 }
 
 // Exclusive scan of the sort histogram, in place, over all (run, species)
-// segments at once: block sums, then each block rescanned, its offset the sum
-// of the blocks before it, which it adds up itself (one read per thread up to
-// 1024 blocks), without a launch between the two that scans the block sums.  A table of one block needs no block sums.  A
-// segment's first entry is then its base and the next segment's first entry
-// (or the grand total) its end.
+// segments at once: block sums, then each block rescanned, its offset the
+// sum of the blocks before it, which it adds up itself (one read per thread
+// up to 1024 blocks), without a launch between the two that scans the block
+// sums.  A table of one block needs no block sums.  A segment's first entry
+// is then its base and the next segment's first entry (or the grand total)
+// its end.
 constexpr int kScanBlock = 8192;
 
 __global__ void k_scan_blocks(const int* h, int64_t n, long long* btot) {
