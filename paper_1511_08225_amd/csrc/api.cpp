@@ -292,9 +292,9 @@ int make_plan(const slpic_run_config* cfg, int nruns, const slpic_tuning* tin, P
             R.hoff[s] = hoff;
             hoff += (int64_t)R.nkeys * R.ntiles[s];
         }
+        R.geom = plates ? kGeomPlates : periodic ? kGeomPeriodic : kGeomSheath;
         R.set_floats();
         R.inj_ratio = R.w[1] / R.w[0];
-        R.geom = plates ? kGeomPlates : periodic ? kGeomPeriodic : kGeomSheath;
         if (plates || periodic) P.all_sheath = false;
         if (c.beta_kind != SLPIC_BETA_STEP) P.all_step = false;
         R.bias = plates ? c.bias : 0.0;

@@ -26,18 +26,19 @@ static_assert(2 * (kFieldThreads / 64) <= kFieldTmp, "each scan of the solve kee
 // field solve: nodes per thread kept in registers (every run's cells fit the
 // 1024-thread workgroup; a longer unrolled row would only cost registers)
 constexpr int kFieldPer = (kMaxCells + kFieldThreads - 1) / kFieldThreads;
+constexpr int kWaveWindow = 128;    // nodes of the push's per-wave LDS charge window
 constexpr int kPlatesMaxSource = 511;   // plates: source_cells + 1 nodes fit the injection LDS window
 constexpr int kInjectThreads = 128;     // plates: particles per wall-injection workgroup
 constexpr int kHistoryLen = 4096;  // wall-potential ring per run
 constexpr int kCountSlots = 64;    // spread slots of the per-step particle counters
 
 // Float copies of the parameters the float push computes with (round to
-// nearest of the FP64 ones).
+// nearest of the FP64 ones), and what else is derived from the others.
 struct RunFloats {
     float qm[kMaxSpecies];
     float dt, u, u2, inv_fscale;
     float dtfx;  // dt/dx in fixed-point units per velocity unit (2^fb dt/dx)
-    float pad;
+    int32_t ring;  // periodic boxes longer than a deposit window: their nodes, else 0
 };
 
 // Immutable per-run parameters (device copy of the host plan).
@@ -82,8 +83,11 @@ struct RunInfo {
         f.u2 = (float)u2;
         f.inv_fscale = (float)inv_fscale;
         f.dtfx = (float)(dtdx * fscale);
-        f.pad = 0.0f;
+        // a box that fits a window from its lowest cell less the margin needs no ring
+        f.ring = geom == kGeomPeriodic && nx + margin() >= kWaveWindow ? nodes : 0;
     }
+    // cells a particle can move in one step (rounded up, plus one; 2 without a limit)
+    __host__ __device__ int margin() const { return uinf ? 2 : (int)fmin(32.0, ceil(umax * dtdx) + 1.0); }
 };
 
 // A new (higher) speed limit for one run: the new limit and the new weights.
