@@ -48,6 +48,22 @@ int clog2(int64_t v) {
     return b;
 }
 
+// The sort tile is an upper bound: with fewer than about 1024 workgroups a
+// sort takes as long as one tile's serial rows.  Whole FP32 steps, a sort in
+// every eighth, at 32768, 8192, 2048 and 1024 slots per tile: 123k particles
+// 69.7, 50.8, 46.5, 46.0 us; 1.6M 98.7, 78.5, 74.9, 73.8; 6.1M 138.8, 118.6,
+// 118.1, 121.9; 16.8M 248.5, 239.4, 245.2, 261.6; 33.6M 397.7, 403.2, 439.9, 517.
+// Tiles stay at least as long as there are keys, so that the (key, tile) table
+// stays below the particles; runs with more than four slots per particle count
+// a quarter of their slots.
+int fit_sort_tile(const slpic_run_config& c, int ny, int nkeys, int tile) {
+    const double cells = (double)c.nx * ny;
+    const double load =
+        cells * ((double)c.species[0].ppc + c.species[1].ppc) * std::max(1.0, c.capacity_factor / 4.0);
+    while (tile % 2048 == 0 && tile / 2 >= nkeys && load < 1024.0 * tile) tile /= 2;
+    return tile;
+}
+
 int make_plan2(const slpic_run_config* c, int ny, const slpic2d_tuning* tin, Plan2& P) {
     if (!c || c->geometry != SLPIC_GEOM_SHEATH) return SLPIC_EINVAL;  // the plates geometry is 1D only
     slpic2d_tuning t{};
@@ -89,7 +105,6 @@ int make_plan2(const slpic_run_config* c, int ny, const slpic2d_tuning* tin, Pla
     if (R.nkeys > 4096) return SLPIC_EINVAL;
     R.margin = t.margin;
     R.win = t.tile + 2 * t.margin + 1;
-    R.sort_tile = t.sort_tile;
     R.tile_shift = (t.tile & (t.tile - 1)) ? -1 : clog2(t.tile);
     R.dx = c->dx;
     R.dt = c->dt;
@@ -105,6 +120,9 @@ int make_plan2(const slpic_run_config* c, int ny, const slpic2d_tuning* tin, Pla
     R.steady_window = c->steady_window > 0 ? c->steady_window : std::max(1, c->nx / 4);
     R.steady_tol = c->steady_tol > 0.0 ? c->steady_tol : 0.02;
     const double cf = c->capacity_factor > 1.0 ? c->capacity_factor : 1.0;
+    t.sort_tile = fit_sort_tile(*c, ny, R.nkeys, t.sort_tile);
+    P.tun.sort_tile = t.sort_tile;
+    R.sort_tile = t.sort_tile;
     int64_t poff = 0, hoff = 0;
     for (int s = 0; s < 2; ++s) {
         const slpic_species& sp = c->species[s];
