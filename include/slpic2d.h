@@ -20,7 +20,8 @@
  *
  * One run per context; its particles are sorted every sort_every steps by
  * blocks of tile x tile cells (stable, dead slots dropped) so that each block
- * is pushed by one workgroup with its node window in LDS.
+ * is pushed by one workgroup (or several, where blocks are few and full) with
+ * its node window in LDS.
  *
  * Memory, ownership, errors and threading as in slpic.h: the caller owns one
  * 256-byte aligned device workspace of slpic2d_workspace_bytes() bytes; the

@@ -38,6 +38,7 @@ struct Plan2 {
     slpic2d_tuning tun{};
     Run2D R{};
     int64_t total_slots = 0, hist_entries = 0;
+    int push_lparts = 0;  // log2 of the push workgroups per sorted tile and species
     size_t push_lds = 0, sort_lds = 0, scatter_lds = 0;
     Layout2 L{};
 };
@@ -46,6 +47,25 @@ int clog2(int64_t v) {
     int b = 0;
     while ((int64_t(1) << b) < v) ++b;
     return b;
+}
+
+// log2 of the workgroups per sorted tile and species in the push.  Doubling them halves
+// what a workgroup pushes one row after another and doubles the windows staged
+// and flushed; over 17 shapes from 16 x 16 to 512 x 512 cells, 4 to 64 per cell,
+// it pays while a workgroup has as many particles as the launch has workgroups.
+// Whole FP32 steps in us at 1, 2, 4, 8 workgroups per tile: 128 tiles of 960
+// particles 46.7, 41.2, 40.2, 40.5; of 3840 79.3, 61.4, 52.3, 48.6; 800 of 1024
+// 56.5, 54.2, 56.8, 69.6; 2432 of 1010 77.5, 80.0; of 2526 118, 111, 127; 8192
+// of 4096 392, 440.  A part is also worth a quarter of the window's nodes.
+int split_push(const slpic_run_config& c, int ny, int nkeys, int win) {
+    double groups = 2.0 * nkeys;
+    double each = (double)c.nx * ny * ((double)c.species[0].ppc + c.species[1].ppc) / groups;
+    int lparts = 0;
+    for (; lparts < 6 && each >= groups && 4.0 * each >= (double)win * win; ++lparts) {
+        each /= 2.0;
+        groups *= 2.0;
+    }
+    return lparts;
 }
 
 // The sort tile is an upper bound: with fewer than about 1024 workgroups a
@@ -123,6 +143,7 @@ int make_plan2(const slpic_run_config* c, int ny, const slpic2d_tuning* tin, Pla
     t.sort_tile = fit_sort_tile(*c, ny, R.nkeys, t.sort_tile);
     P.tun.sort_tile = t.sort_tile;
     R.sort_tile = t.sort_tile;
+    P.push_lparts = split_push(*c, ny, R.nkeys, R.win);
     int64_t poff = 0, hoff = 0;
     for (int s = 0; s < 2; ++s) {
         const slpic_species& sp = c->species[s];
@@ -242,8 +263,10 @@ int timed2(Ctx2* c, int k, hipStream_t s, F&& f) {
 int push2(Ctx2* c, bool push, hipStream_t s) {
     const Plan2& P = c->P;
     int rc = 0;
-    if (f32(c)) rc = launch2d_push_f32(push, P.tun.per_thread, c->a, P.R.nkeys, P.tun.tail_groups, P.push_lds, s);
-    else rc = launch2d_push_f64(push, P.tun.per_thread, c->a, P.R.nkeys, P.tun.tail_groups, P.push_lds, s);
+    if (f32(c)) rc = launch2d_push_f32(push, P.tun.per_thread, c->a, P.R.nkeys, P.push_lparts, P.tun.tail_groups,
+                                       P.push_lds, s);
+    else rc = launch2d_push_f64(push, P.tun.per_thread, c->a, P.R.nkeys, P.push_lparts, P.tun.tail_groups,
+                                P.push_lds, s);
     return rc ? SLPIC_EINVAL : SLPIC_OK;
 }
 

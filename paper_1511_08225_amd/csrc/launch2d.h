@@ -11,7 +11,8 @@ namespace slpic {
 
 #define SLPIC2_DECLARE_LAUNCHERS(sfx)                                                                    \
     void launch2d_load_##sfx(const Args2D& a, hipStream_t s);                                            \
-    int launch2d_push_##sfx(bool push, int per_thread, const Args2D& a, int nkeys, int ntail, size_t lds, \
+    int launch2d_push_##sfx(bool push, int per_thread, const Args2D& a, int nkeys, int lparts,         \
+                            int ntail, size_t lds,                                                     \
                             hipStream_t s);                                                              \
     void launch2d_inject_##sfx(const Args2D& a, int groups, hipStream_t s);                              \
     void launch2d_sort_hist_##sfx(const Args2D& a, int ntiles, size_t lds, hipStream_t s);               \
