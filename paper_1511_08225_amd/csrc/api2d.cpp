@@ -307,7 +307,6 @@ int one_step2(Ctx2* c, int64_t index, hipStream_t s) {
     if ((rc = timed2(c, 1, s, [&] {
              if (f32(c)) launch2d_inject_f32(c->a, kInjectGroups2, s);
              else launch2d_inject_f64(c->a, kInjectGroups2, s);
-             launch2d_finish(c->a, s);
          })))
         return rc;
     if ((rc = field2(c, s, 1))) return rc;  // with Phi_w into the history ring and the steady detector
