@@ -48,8 +48,9 @@ typedef float f32x4a __attribute__((ext_vector_type(4), aligned(4)));  // of cal
 
 // ---------------------------------------------------------------------------
 // Forward pass in one launch.  A workgroup of 16 wavefronts takes 16 RT batch
-// rows and 256 of the 1792 outputs; it computes the three hidden layers of
-// its rows itself (7 workgroups repeat them for one row block), wavefront w
+// rows and 256 CB of the 1792 outputs; it computes the three hidden layers of
+// its rows itself (with CB = 1 7 workgroups repeat them for one row block; with
+// CB = 7 one walks all the outputs, for large batches), wavefront w
 // the columns 16 w .. 16 w + 15 of every layer with gfx950's
 // v_mfma_f32_16x16x32_bf16 (lane l holds A row l % 16 and B column l % 16 at
 // k = 8 (l / 16) + 0..7; the accumulator holds rows 4 (l / 16) + 0..3 of
@@ -104,7 +105,7 @@ __device__ __forceinline__ void row_products(const bf16 (*H)[kFwdLdsRow], int i,
                                                              acc[t], 0, 0, 0);
 }
 
-template <int RT>
+template <int RT, int CB>
 __global__ __launch_bounds__(kFwdThreads) void k_forward(const bf16* __restrict__ P, const float* __restrict__ x,
                                                          float* __restrict__ y, int batch, bf16* __restrict__ act) {
     constexpr int kRows = 16 * RT;
@@ -112,7 +113,9 @@ __global__ __launch_bounds__(kFwdThreads) void k_forward(const bf16* __restrict_
     __shared__ __align__(16) bf16 X[kFwdThreads / 64][16][kXRow];
     __shared__ float xs[kRows][kIn];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i = lane & 15, kq = lane >> 4;
-    const int b0 = (int)(blockIdx.x / (kOut / kFwdCols)) * kRows, c0 = (int)(blockIdx.x % (kOut / kFwdCols)) * kFwdCols;
+    constexpr int kGroups = kOut / kFwdCols / CB;  // workgroups of a row block
+    static_assert(kGroups * CB * kFwdCols == kOut, "whole column blocks");
+    const int b0 = (int)(blockIdx.x / kGroups) * kRows, c0 = (int)(blockIdx.x % kGroups) * CB * kFwdCols;
     const int rows = min(kRows, batch - b0);
     const int n = 16 * w + i;  // this lane's column of every layer
     const int j1 = threadIdx.x & (kHid - 1), r1 = threadIdx.x / kHid;  // layer 1: one column, every fourth row
@@ -161,16 +164,27 @@ __global__ __launch_bounds__(kFwdThreads) void k_forward(const bf16* __restrict_
                 if (keep && row < rows) ho[(int64_t)(b0 + row) * kHid + n] = h;
             }
     }
-    to_fragments(X[w], lane, f[0]);
-    __syncthreads();
-    row_products<RT>(H, i, kq, f[0], acc);
+    float b4 = bias[2];
 #pragma unroll
-    for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = 16 * t + 4 * kq + r;
-            if (row < rows) y[(int64_t)(b0 + row) * kOut + c0 + n] = acc[t][r] + bias[2];
+    for (int cb = 0; cb < CB; ++cb) {  // the output layer, a column block after the other
+        const int c = c0 + cb * kFwdCols;
+        float next = 0.f;
+        if (cb + 1 < CB) {
+            load_rows(P + oW4, c + kFwdCols + 16 * w, lane, f[(cb + 1) & 1]);
+            next = from_bf16(P[ob4 + c + kFwdCols + n]);
         }
+        to_fragments(X[w], lane, f[cb & 1]);
+        if (cb == 0) __syncthreads();
+        row_products<RT>(H, i, kq, f[cb & 1], acc);
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = 16 * t + 4 * kq + r;
+                if (row < rows) y[(int64_t)(b0 + row) * kOut + c + n] = acc[t][r] + b4;
+            }
+        b4 = next;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -439,12 +453,22 @@ static int last_error() { return hipGetLastError() == hipSuccess ? SLPIC_OK : SL
 // activations go to act ([batch][4 + 3 * 256] BF16; null: not stored), the
 // output to y.
 static int forward_impl(const bf16* P, const float* x, float* y, int32_t batch, bf16* act, hipStream_t s) {
-    auto grid = [&](int rt) { return (unsigned)((batch + 16 * rt - 1) / (16 * rt)) * (kOut / kFwdCols); };
-    // 16 rows a workgroup while they all fit the chip's 256 CUs at once (one
-    // fits a CU), 32 rows beyond: batch 512 takes 10.3 us with 16 rows and
-    // 12.8 with 32, batch 1024 19.0 and 13.4
-    if (grid(1) <= 256) hipLaunchKernelGGL(k_forward<1>, dim3(grid(1)), dim3(kFwdThreads), 0, s, P, x, y, batch, act);
-    else hipLaunchKernelGGL(k_forward<2>, dim3(grid(2)), dim3(kFwdThreads), 0, s, P, x, y, batch, act);
+    // The variant that repeats the least work among those whose workgroups all
+    // fit the chip's 256 CUs at once (one fits a CU): a second round costs as much
+    // as the first.  us a call with <rows / 16, output blocks per workgroup> <1, 1>,
+    // <2, 1>, <1, 7>, <2, 7>: batch 512 11.2, 13.3, 20.2, 25.3; 1024 19.9, 14.2, 20.7,
+    // 26.0; 1184 27.8, 24.1, 20.9, 26.0; 4096 62.0, 46.1, 23.6, 28.3; 8192 122, 80,
+    // 41.9, 29.7; 16384 242, 157, 80, 53 (a launch per layer 19.6, 22.4, 24.5, 41.8,
+    // 66.8, 120)
+    constexpr int kCus = 256, kBlocks = kOut / kFwdCols;
+    auto rows = [&](int rt) { return (batch + 16 * rt - 1) / (16 * rt); };
+    auto launch = [&](auto kernel, int groups) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(kFwdThreads), 0, s, P, x, y, batch, act);
+    };
+    if ((int64_t)rows(1) * kBlocks <= kCus) launch(k_forward<1, 1>, rows(1) * kBlocks);
+    else if ((int64_t)rows(2) * kBlocks <= kCus) launch(k_forward<2, 1>, rows(2) * kBlocks);
+    else if (rows(1) <= kCus) launch(k_forward<1, kBlocks>, rows(1));
+    else launch(k_forward<2, kBlocks>, rows(2));
     return last_error();
 }
 
