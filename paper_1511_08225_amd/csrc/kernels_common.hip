@@ -49,12 +49,13 @@ __global__ __launch_bounds__(kFieldThreads) void k_field(KArgs a, int advance) {
 }
 
 // Exclusive scan of the sort histogram, in place, over all (run, species)
-// segments at once: block sums, then each block rescanned, its offset the
-// sum of the blocks before it, which it adds up itself (one read per thread
-// up to 1024 blocks), without a launch between the two that scans the block
-// sums.  A table of one block needs no block sums.  A segment's first entry
-// is then its base and the next segment's first entry (or the grand total)
-// its end.
+// segments at once: block sums, then each block rescanned with its offset,
+// the sum of the blocks before it.  Up to kScanOwnBlocks blocks add that up
+// themselves, without a launch between the two; more have the block sums
+// scanned first (k_scan_top), since the reads of all blocks together grow with
+// the square of their number.  A table of one block needs no block sums.  A
+// segment's first entry is then its base and the next segment's first entry
+// (or the grand total) its end.
 constexpr int kScanBlock = 8192;
 
 __global__ void k_scan_blocks(const int* h, int64_t n, long long* btot) {
@@ -68,14 +69,30 @@ __global__ void k_scan_blocks(const int* h, int64_t n, long long* btot) {
     if (threadIdx.x == blockDim.x - 1) btot[blockIdx.x] = ex + loc;
 }
 
+// Block sums to their exclusive scan, the grand total at btot[nblk].  One workgroup.
+__global__ void k_scan_top(long long* btot, int nblk) {
+    __shared__ long long tmp[17];
+    const int per = (nblk + blockDim.x - 1) / blockDim.x;
+    const int j0 = min((int)threadIdx.x * per, nblk), j1 = min(j0 + per, nblk);
+    long long loc = 0;
+    for (int j = j0; j < j1; ++j) loc += btot[j];
+    long long run = block_scan<long long>(loc, tmp, false);
+    for (int j = j0; j < j1; ++j) {
+        long long c = btot[j];
+        btot[j] = run;
+        run += c;
+    }
+    if (threadIdx.x == blockDim.x - 1) btot[nblk] = run;
+}
+
 // Launched with kScanThreads threads: each holds kScanPer consecutive
 // entries in registers (two 16-byte loads and stores where all are in range;
-// h is 16-byte aligned).  The last block writes the grand total to
-// btot[gridDim.x].
+// h is 16-byte aligned).  scanned: btot holds the blocks' offsets, else their
+// sums, and the last block writes the grand total to btot[gridDim.x].
 constexpr int kScanThreads = 1024;
 constexpr int kScanPer = kScanBlock / kScanThreads;
 static_assert(kScanPer == 8, "two int4 per thread");
-__global__ __launch_bounds__(kScanThreads) void k_scan_apply(int* h, int64_t n, long long* btot) {
+__global__ __launch_bounds__(kScanThreads) void k_scan_apply(int* h, int64_t n, long long* btot, int scanned) {
     __shared__ long long tmp[17], before[1];
     const int64_t j0 = (int64_t)blockIdx.x * kScanBlock + (int64_t)threadIdx.x * kScanPer;
     const bool full = j0 + kScanPer <= n;
@@ -88,10 +105,14 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(int* h, int64_t n, 
 #pragma unroll
         for (int i = 0; i < kScanPer; ++i) v[i] = j0 + i < n ? h[j0 + i] : 0;
     }
-    long long prev = 0;
-    for (int j = threadIdx.x; j < (int)blockIdx.x; j += kScanThreads) prev += btot[j];
-    const long long pex = block_scan<long long>(prev, tmp, false);
-    if (threadIdx.x == kScanThreads - 1) before[0] = pex + prev;
+    if (scanned) {
+        if (threadIdx.x == 0) before[0] = btot[blockIdx.x];
+    } else {
+        long long prev = 0;
+        for (int j = threadIdx.x; j < (int)blockIdx.x; j += kScanThreads) prev += btot[j];
+        const long long pex = block_scan<long long>(prev, tmp, false);
+        if (threadIdx.x == kScanThreads - 1) before[0] = pex + prev;
+    }
     long long loc = 0;
 #pragma unroll
     for (int i = 0; i < kScanPer; ++i) loc += v[i];
@@ -111,7 +132,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(int* h, int64_t n, 
         for (int i = 0; i < kScanPer; ++i)
             if (j0 + i < n) h[j0 + i] = o[i];
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kScanThreads - 1) btot[gridDim.x] = run;
+    if (!scanned && blockIdx.x == gridDim.x - 1 && threadIdx.x == kScanThreads - 1) btot[gridDim.x] = run;
 }
 
 // After the scatter: the sorted buffer becomes current and holds exactly the
@@ -209,11 +230,18 @@ void launch_init_state(const KArgs& a, int nruns, hipStream_t s) {
 void launch_field(const KArgs& a, int nruns, int advance, size_t lds, hipStream_t s) {
     hipLaunchKernelGGL(k_field, dim3(nruns), dim3(kFieldThreads), lds, s, a, advance);
 }
+// The line between the two: own sums and scanned sums take 6.7 and 8.1 us at 2
+// blocks, 11.4 and 13.0 at 512, 19.4 and 20.3 at 1024, 34.7 and 33.4 at 1536, 79.5
+// and 70.6 at 4096, 422 and 386 at 16384, 7173 and 3168 at 131072 (a change of
+// speed limit scans an entry per slot).
+constexpr int kScanOwnBlocks = 1024;
 int scan_blocks(int64_t n) { return (int)((n + kScanBlock - 1) / kScanBlock); }
 void launch_scan_ints(int* h, int64_t n, long long* btot, hipStream_t s) {
     const int nblk = scan_blocks(n);
+    const int top = nblk > kScanOwnBlocks;
     if (nblk > 1) hipLaunchKernelGGL(k_scan_blocks, dim3(nblk), dim3(1024), 0, s, (const int*)h, n, btot);
-    hipLaunchKernelGGL(k_scan_apply, dim3(nblk), dim3(kScanThreads), 0, s, h, n, btot);
+    if (top) hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, btot, nblk);
+    hipLaunchKernelGGL(k_scan_apply, dim3(nblk), dim3(kScanThreads), 0, s, h, n, btot, top);
 }
 void launch_sort_scan(const KArgs& a, int64_t hist_entries, long long* btot, hipStream_t s) {
     launch_scan_ints(a.hist, hist_entries, btot, s);
