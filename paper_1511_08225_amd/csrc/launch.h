@@ -19,7 +19,7 @@ namespace slpic {
     void launch_wall_inject_##sfx(const KArgs& a, hipStream_t s);                                      \
     void launch_limit_##sfx(const KArgs& a, const LimitArgs& L, int nchunks, int scatter, hipStream_t s); \
     void launch_moments_##sfx(const KArgs& a, int chunk0, int nchunks, int chunk, double* out,         \
-                              int per_run, int phi_runs, hipStream_t s);                               \
+                              int per_run, int phi_runs, bool ordered, int max_nodes, hipStream_t s);                               \
     void launch_sort_hist_##sfx(const KArgs& a, int ntiles, int block, size_t lds, int whole,          \
                                 hipStream_t s);                                                        \
     void launch_sort_scatter_##sfx(const KArgs& a, int ntiles, int block, size_t lds, hipStream_t s);
