@@ -223,6 +223,7 @@ struct Ctx2 {
     Args2D a{};
     unsigned char* ws = nullptr;
     int64_t steps_done = 0;
+    bool sorted = false;  // particles sorted since the load or the last import
     int prof = 0;
     std::vector<Ev2> ev[4];
     size_t ev_used[4] = {0, 0, 0, 0};
@@ -273,6 +274,7 @@ int push2(Ctx2* c, bool push, hipStream_t s) {
 int sort2(Ctx2* c, hipStream_t s) {
     const Plan2& P = c->P;
     const int nt = P.R.stiles[0] + P.R.stiles[1];
+    c->sorted = true;
     return timed2(c, 3, s, [&] {
         // the (key, tile) counts start at zero: a tile writes only the keys it holds
         launch_zero_ints(c->a.hist, P.hist_entries, s);
@@ -484,8 +486,9 @@ int slpic2d_moments(void* ctx, double* d_out, void* stream) {
     hipStream_t s = (hipStream_t)stream;
     const Run2D& R = c->P.R;
     launch2d_fill(d_out, 7 * R.nodes, s);
-    if (f32(c)) launch2d_moments_f32(c->a, R.nkeys, R.win, std::max(R.cap[0], R.cap[1]), d_out, s);
-    else launch2d_moments_f64(c->a, R.nkeys, R.win, std::max(R.cap[0], R.cap[1]), d_out, s);
+    const int64_t slots = std::max(R.cap[0], R.cap[1]);
+    if (f32(c)) launch2d_moments_f32(c->a, R.nkeys, R.win, slots, !c->sorted, d_out, s);
+    else launch2d_moments_f64(c->a, R.nkeys, R.win, slots, !c->sorted, d_out, s);
     launch2d_moments_finish(c->a, R.nodes, d_out, s);
     return hipGetLastError() == hipSuccess ? SLPIC_OK : SLPIC_EHIP;
 }
@@ -631,6 +634,7 @@ int slpic2d_import_particles(void* ctx, int32_t species, const double* h_x, cons
     }
     st.nslots[species] = n;
     st.nsorted[species] = 0;
+    c->sorted = false;
     HIP2_TRY(hipMemcpy(c->a.st, &st, sizeof(State2D), hipMemcpyHostToDevice));
     return SLPIC_OK;
 }

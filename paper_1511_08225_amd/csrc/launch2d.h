@@ -17,7 +17,8 @@ namespace slpic {
     void launch2d_inject_##sfx(const Args2D& a, int groups, hipStream_t s);                              \
     void launch2d_sort_hist_##sfx(const Args2D& a, int ntiles, size_t lds, hipStream_t s);               \
     void launch2d_sort_scatter_##sfx(const Args2D& a, int ntiles, size_t lds, hipStream_t s);          \
-    void launch2d_moments_##sfx(const Args2D& a, int nkeys, int win, int64_t slots, double* out, hipStream_t s);
+    void launch2d_moments_##sfx(const Args2D& a, int nkeys, int win, int64_t slots, bool tailed,      \
+                               double* out, hipStream_t s);
 
 SLPIC2_DECLARE_LAUNCHERS(f32)
 SLPIC2_DECLARE_LAUNCHERS(f64)

@@ -124,3 +124,31 @@ def test_moments_follow_the_order(gpu_lib, kw):
             assert rel_inf(win[row], one[row]) <= TOL, row
         check()
     sim.close()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_unsorted_2d_moments_written_out(gpu_lib, prec):
+    """The 2D pass before any sort, after one, and with one species imported
+    since, whose slots are then unsorted while the other's tiles are not."""
+    from test_gpu_moments import _plane_moments
+    ny = 32
+    cfg = workloads.sheath2d(70, ny, 60, 3.0, tile=8, seed=5)
+    sim = gpu_lib.Sim2D(cfg, ny, precision=prec, sort_every=0, tile=8, margin=2)
+
+    def check(what):
+        print_case(f"2D moments {what} {prec}")
+        got, want = sim.moments().cpu().numpy(), _plane_moments(sim, cfg, ny)
+        for row in range(6):
+            assert rel_inf(got[1 + row], want[row]) <= TOL, (what, row)
+    check("never sorted")
+    sim.sort_now()
+    check("sorted")
+    sim.step(5)
+    check("five steps on")
+    p = sim.export_particles(1)
+    o = np.random.default_rng(1).permutation(len(p[0]))
+    sim.import_particles(1, *(a[o] for a in p))
+    check("ions imported")
+    sim.sort_now()
+    check("sorted again")
+    sim.close()
