@@ -147,18 +147,24 @@ typedef struct {
                            /* the warm cells take that limit too.  1D only.    */
 } slpic_run_config;
 
+/* Or-ed to a tuning's chunk or sort_tile (0 included): that value, whatever the
+ * size of the run set. */
+#define SLPIC_EXACT 0x40000000
+
 typedef struct {
     int32_t precision;    /* SLPIC_F32 / SLPIC_F64 (all runs of a context)          */
     int32_t sort_every;   /* stable cell sort + compaction every k steps; 0 = never  */
     int32_t sort_bucket;  /* sort key = cell / bucket; 0 = compaction only (key 0)   */
     int32_t chunk;        /* particles per push wavefront, at most: 64 P, P in {1,   */
                           /* 2, 4, 8, 16}; 0 = default (512 for F32, 256 for F64).   */
-                          /* Run sets too small to fill the chip take fewer          */
+                          /* Run sets too small to fill the chip take fewer; with    */
+                          /* SLPIC_EXACT or-ed to it, just as many                   */
     int32_t block;        /* threads per push workgroup: 64, 128, 192 or 256, one   */
                           /* wavefront per chunk; 0 = default (128)                  */
     int32_t graph_steps;  /* steps captured per HIP graph; 0 = direct launches       */
     int32_t sort_tile;    /* particles per sort workgroup, at most (<= 32768; 0 =    */
-                          /* 16384): small run sets take fewer                       */
+                          /* 16384): small run sets take fewer; with SLPIC_EXACT     */
+                          /* or-ed to it, just as many                               */
     int32_t retire_steady;/* 1: a run stops advancing (push, source, field solve and */
                           /* step count frozen) from the step after its steady      */
                           /* detector flags it; 0 = every run always advances       */
@@ -306,6 +312,10 @@ int slpic_refresh_fields(void* ctx, void* stream);
  * doubles, Q_j = sum q w beta W_j, so rho_j = Q_j/dV_j), potential and
  * field at the nodes.  Any pointer may be NULL. */
 int slpic_export_grid(void* ctx, int32_t run, double* h_Q, double* h_phi, double* h_E);
+
+/* The chunk and the sort tile of the context's launches, in slots (host only).
+ * Either pointer may be NULL. */
+int slpic_launch_shape(void* ctx, int32_t* chunk, int32_t* sort_tile);
 
 /* Run the stable cell sort (compaction) of every run now.  Async. */
 int slpic_sort_now(void* ctx, void* stream);

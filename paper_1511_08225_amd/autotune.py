@@ -7,7 +7,10 @@ trials of the real step on the GPU (coordinate descent over the candidate
 lists), and caches the choice per workload signature in a JSON file so that
 later contexts over similar run sets start tuned.  The sort schedule changes
 only the slot order (the physics is the same up to FP64 summation order), so
-every candidate is a valid setting.
+every candidate is a valid setting.  Chunk and sort tile are upper bounds of
+what a launch takes (slpic.EXACT is not set): on a small run set several
+candidates start the same launch, and a trial replaces the incumbent only
+beyond the noise.
 """
 from __future__ import annotations
 

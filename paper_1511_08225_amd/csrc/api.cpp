@@ -151,8 +151,8 @@ struct Plan {
     Layout L{};
 };
 
-// The push chunk and the sort tile are upper bounds: a run set too small to
-// fill the chip with them takes smaller ones.  A wavefront works through its
+// The push chunk and the sort tile are upper bounds (but for SLPIC_EXACT): a run
+// set too small to fill the chip with them takes smaller ones.  A wavefront works through its
 // P particles per lane one after another, so with fewer than about
 // kMinPushWaves wavefronts (two per SIMD) the launch takes as long as one of
 // them: whole FP32 steps of 517k particles take 30.3, 24.0, 24.1 us at 512,
@@ -166,15 +166,15 @@ struct Plan {
 // larger, are slower.  Launches and the sort's table go by the slots, so a
 // run with more than four per particle loaded counts a quarter of its slots:
 // empty wavefronts cost 0.2 us per 1000.
-void fit_launch(const slpic_run_config* cfg, int nruns, slpic_tuning& t) {
+void fit_launch(const slpic_run_config* cfg, int nruns, slpic_tuning& t, bool fit_chunk, bool fit_tile) {
     constexpr double kMinPushWaves = 2048.0, kMinSortTiles = 512.0;
     constexpr int kMinSortTile = 1024;
     double load = 0.0;
     for (int r = 0; r < nruns; ++r)
         for (int s = 0; s < 2; ++s)
             load += (double)cfg[r].nx * (double)cfg[r].species[s].ppc * std::max(1.0, cfg[r].capacity_factor / 4.0);
-    while (t.chunk > 64 && load < kMinPushWaves * t.chunk) t.chunk /= 2;
-    while (t.sort_tile >= 2 * kMinSortTile && load < kMinSortTiles * t.sort_tile) t.sort_tile /= 2;
+    while (fit_chunk && t.chunk > 64 && load < kMinPushWaves * t.chunk) t.chunk /= 2;
+    while (fit_tile && t.sort_tile >= 2 * kMinSortTile && load < kMinSortTiles * t.sort_tile) t.sort_tile /= 2;
 }
 
 int make_plan(const slpic_run_config* cfg, int nruns, const slpic_tuning* tin, Plan& P) {
@@ -186,6 +186,9 @@ int make_plan(const slpic_run_config* cfg, int nruns, const slpic_tuning* tin, P
         t.sort_tile < 0 || (t.retire_steady != 0 && t.retire_steady != 1) ||
         (t.push_order != 0 && t.push_order != 1) || (t.record_perm != 0 && t.record_perm != 1))
         return SLPIC_EINVAL;
+    const bool fit_chunk = !(t.chunk & SLPIC_EXACT), fit_tile = !(t.sort_tile & SLPIC_EXACT);
+    t.chunk &= ~SLPIC_EXACT;
+    t.sort_tile &= ~SLPIC_EXACT;
     if (t.block == 0) t.block = 128;
     if (t.chunk == 0) t.chunk = 64 * (t.precision == SLPIC_F32 ? 8 : 4);
     if (t.sort_tile == 0) t.sort_tile = 16384;
@@ -198,7 +201,7 @@ int make_plan(const slpic_run_config* cfg, int nruns, const slpic_tuning* tin, P
     }
     if (t.sort_every > 0 && t.graph_steps > 0 && t.graph_steps % t.sort_every)
         t.graph_steps = (t.graph_steps / t.sort_every + 1) * t.sort_every;
-    fit_launch(cfg, nruns, t);
+    fit_launch(cfg, nruns, t, fit_chunk, fit_tile);
     P.tun = t;
     P.nruns = nruns;
     P.runs.assign(nruns, RunInfo{});
@@ -1080,6 +1083,14 @@ int slpic_export_grid(void* ctx, int32_t run, double* h_Q, double* h_phi, double
         if (int rc = copy_d2h(h_phi, c->a.phi + R.goff, sizeof(double) * R.nodes)) return rc;
     if (h_E)
         if (int rc = copy_d2h(h_E, c->a.E + R.goff, sizeof(double) * R.nodes)) return rc;
+    return SLPIC_OK;
+}
+
+int slpic_launch_shape(void* ctx, int32_t* chunk, int32_t* sort_tile) {
+    Context* c = ctx_of(ctx);
+    if (!c) return SLPIC_EINVAL;
+    if (chunk) *chunk = c->P.tun.chunk;
+    if (sort_tile) *sort_tile = c->P.tun.sort_tile;
     return SLPIC_OK;
 }
 

@@ -68,7 +68,7 @@ int split_push(const slpic_run_config& c, int ny, int nkeys, int win) {
     return lparts;
 }
 
-// The sort tile is an upper bound: with fewer than about 1024 workgroups a
+// The sort tile is an upper bound (but for SLPIC_EXACT): with fewer than about 1024 workgroups a
 // sort takes as long as one tile's serial rows.  Whole FP32 steps, a sort in
 // every eighth, at 32768, 8192, 2048 and 1024 slots per tile: 123k particles
 // 69.7, 50.8, 46.5, 46.0 us; 1.6M 98.7, 78.5, 74.9, 73.8; 6.1M 138.8, 118.6,
@@ -99,6 +99,8 @@ int make_plan2(const slpic_run_config* c, int ny, const slpic2d_tuning* tin, Pla
     if (t.margin == 0) t.margin = std::max(1, t.sort_every);
     if (t.per_thread == 0) t.per_thread = 1;
     if (t.tail_groups == 0) t.tail_groups = 512;
+    const bool fit_tile = !(t.sort_tile & SLPIC_EXACT);
+    t.sort_tile &= ~SLPIC_EXACT;
     if (t.sort_tile == 0) t.sort_tile = 32768;  // 512 x 512 sheath: 0.392 ms per step (65536: 0.402)
     // the scatter keeps per-wave offsets within a tile's run of one key in 16 bits
     if (t.sort_tile < 1024 || t.sort_tile > 32768 || (t.sort_tile & 1023)) return SLPIC_EINVAL;
@@ -140,7 +142,7 @@ int make_plan2(const slpic_run_config* c, int ny, const slpic2d_tuning* tin, Pla
     R.steady_window = c->steady_window > 0 ? c->steady_window : std::max(1, c->nx / 4);
     R.steady_tol = c->steady_tol > 0.0 ? c->steady_tol : 0.02;
     const double cf = c->capacity_factor > 1.0 ? c->capacity_factor : 1.0;
-    t.sort_tile = fit_sort_tile(*c, ny, R.nkeys, t.sort_tile);
+    if (fit_tile) t.sort_tile = fit_sort_tile(*c, ny, R.nkeys, t.sort_tile);
     P.tun.sort_tile = t.sort_tile;
     R.sort_tile = t.sort_tile;
     P.push_lparts = split_push(*c, ny, R.nkeys, R.win);

@@ -18,6 +18,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libslpic.so")
 
 SLPIC_F32, SLPIC_F64 = 0, 1
+EXACT = 0x40000000  # or-ed to chunk or sort_tile: that value, whatever the size of the run set
 GEOM_SHEATH, GEOM_PLATES, GEOM_PERIODIC = 0, 1, 2
 BETA_STEP, BETA_SMOOTH = 0, 1
 FLAG_CAPACITY, FLAG_NUMERIC = 1, 2
@@ -146,6 +147,7 @@ def lib():
             "slpic_prune_retired": (ctypes.c_int, [_P, _PI32, _P]),
             "slpic_refresh_fields": (ctypes.c_int, [_P, _P]),
             "slpic_export_grid": (ctypes.c_int, [_P, i32, _PD, _PD, _PD]),
+            "slpic_launch_shape": (ctypes.c_int, [_P, _PI32, _PI32]),
             "slpic_sort_now": (ctypes.c_int, [_P, _P]),
             "slpic_export_perm": (ctypes.c_int, [_P, i32, i32, _PI32, _PI64]),
             "slpic_profile": (ctypes.c_int, [_P, i32]),
@@ -273,7 +275,9 @@ class Sim:
         array of predicted profiles (phi, n_e, n_i, Gamma_e, Gamma_i, T_e,
         T_i on x/L = k/255; a (5, 256) array loads at the source
         temperatures) for a warm load instead of the cold one.
-        record_perm: every sort also stores its permutation (for perm())."""
+        record_perm: every sort also stores its permutation (for perm()).
+        chunk and sort_tile are upper bounds, of which a small run set takes
+        less; with EXACT or-ed to them they are taken as they are."""
         if isinstance(configs, dict):
             configs = [configs]
         self.configs = [dict(c) for c in configs]
@@ -332,6 +336,12 @@ class Sim:
 
     def refresh_fields(self):
         _check(lib().slpic_refresh_fields(self._ctx, self._stream()), "slpic_refresh_fields")
+
+    def launch_shape(self) -> tuple[int, int]:
+        """The push chunk and the sort tile of this context's launches, in slots."""
+        chunk, tile = ctypes.c_int32(), ctypes.c_int32()
+        _check(lib().slpic_launch_shape(self._ctx, ctypes.byref(chunk), ctypes.byref(tile)), "slpic_launch_shape")
+        return chunk.value, tile.value
 
     def sort_now(self):
         _check(lib().slpic_sort_now(self._ctx, self._stream()), "slpic_sort_now")
