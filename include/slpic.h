@@ -407,7 +407,7 @@ const char* slpic_strerror(int code);
 
 /* Bytes of the activation buffer written by forward and read by backward
  * (BF16 inputs and the three hidden activations), and of backward's
- * scratch buffer (BF16 output and hidden gradients). */
+ * scratch buffer (the three hidden layers' BF16 gradients). */
 size_t slpic_mlp_act_bytes(int32_t batch);
 size_t slpic_mlp_work_bytes(int32_t batch);
 
@@ -424,7 +424,9 @@ int slpic_mlp_forward(const void* d_params_bf16, const float* d_x, float* d_y, i
  * harnesses that forbid hipMalloc): the same kernel and the same d_y, with the
  * activations not stored at all (they stay in the workgroups' LDS).  It calls
  * no allocator and keeps nothing between calls; calls may overlap.  batch
- * beyond SLPIC_MLP_NOALLOC_MAX_BATCH returns SLPIC_ELIMIT. */
+ * beyond SLPIC_MLP_NOALLOC_MAX_BATCH returns SLPIC_ELIMIT: the call's contract
+ * from when it had an array of that size, which callers may rely on; no
+ * resource stands behind it now. */
 #define SLPIC_MLP_NOALLOC_MAX_BATCH 1024
 int slpic_mlp_forward_noalloc(const void* d_params_bf16, const float* d_x, float* d_y, int32_t batch,
                               void* stream);

@@ -478,7 +478,7 @@ size_t slpic_mlp_act_bytes(int32_t batch) {
     return batch > 0 ? (size_t)batch * (kIn + 3 * kHid) * sizeof(bf16) : 0;
 }
 size_t slpic_mlp_work_bytes(int32_t batch) {
-    return batch > 0 ? (size_t)batch * (kOut + 3 * kHid) * sizeof(bf16) : 0;
+    return batch > 0 ? (size_t)batch * 3 * kHid * sizeof(bf16) : 0;
 }
 
 int slpic_mlp_to_bf16(const float* d_params_fp32, void* d_params_bf16, void* stream) {
@@ -511,7 +511,7 @@ int slpic_mlp_backward(const void* d_params_bf16, const void* d_act, const float
     const bf16* h1 = xr + (int64_t)batch * kIn;
     const bf16* h2 = h1 + (int64_t)batch * kHid;
     const bf16* h3 = h2 + (int64_t)batch * kHid;
-    bf16* d3 = (bf16*)d_work + (int64_t)batch * kOut;
+    bf16* d3 = (bf16*)d_work;
     bf16* d2 = d3 + (int64_t)batch * kHid;
     bf16* d1 = d2 + (int64_t)batch * kHid;
     float* g = d_grads;

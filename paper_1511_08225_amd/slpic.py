@@ -516,8 +516,8 @@ class Mlp:
 
     def forward_noalloc(self, x, y=None) -> torch.Tensor:
         """The same forward pass through slpic_mlp_forward_noalloc: the
-        activations are not stored (nothing for backward); y [n][1792] is written for x [n][4], n a multiple of 16 up
-        to MLP_NOALLOC_MAX_BATCH."""
+        activations are not stored (nothing for backward); y [n][1792] is
+        written for x [n][4], n a multiple of 16 up to MLP_NOALLOC_MAX_BATCH."""
         x = torch.as_tensor(x, dtype=torch.float32).to(self.device).contiguous()
         if x.dim() != 2 or x.shape[1] != MLP_IN:
             raise SlpicError("x must be [n][4]")
