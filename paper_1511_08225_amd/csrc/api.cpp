@@ -166,14 +166,28 @@ struct Plan {
 // larger, are slower.  Launches and the sort's table go by the slots, so a
 // run with more than four per particle loaded counts a quarter of its slots:
 // empty wavefronts cost 0.2 us per 1000.
+// A context that does not sort its slots by cell (or by keys far longer than a
+// window: at 200 cells either rule is within 5 %) deposits most charge with global
+// atomics, fewer the more particles share a wavefront's window and its flush:
+// chunks are halved only below kMinLooseWaves wavefronts (plates: of their filled
+// slots).  Never sorted FP32 steps in us at 512, 256, 128, 64 slots: 200k particles
+// on 100 cells 21.7, 23.1, 27.0, 31.9, 517k on 777 128.7, 140.4, 161.2, 167.8, 240k on
+// 1500 39.2, 39.7, 46.7, 53.5, but 102k on 64 15.5, 14.4, 14.8, 15.3 and 12.6k on 300
+// 17.9, 14.4, 13.9, 13.3; FP64 at 256, 128, 64: 200k on 100 30.1, 36.3, 43.0, 240k on
+// 1500 45.6, 70.9, 49.9, 24k on 200 20.9, 16.0, 13.8.
 void fit_launch(const slpic_run_config* cfg, int nruns, slpic_tuning& t, bool fit_chunk, bool fit_tile) {
-    constexpr double kMinPushWaves = 2048.0, kMinSortTiles = 512.0;
+    constexpr double kMinPushWaves = 2048.0, kMinLooseWaves = 256.0, kMinSortTiles = 512.0;
     constexpr int kMinSortTile = 1024;
-    double load = 0.0;
+    const bool sorts = t.sort_every > 0 && t.sort_bucket > 0 && t.sort_bucket <= 2 * kWaveWindow;
+    double load = 0.0, filled = 0.0;
     for (int r = 0; r < nruns; ++r)
-        for (int s = 0; s < 2; ++s)
-            load += (double)cfg[r].nx * (double)cfg[r].species[s].ppc * std::max(1.0, cfg[r].capacity_factor / 4.0);
-    while (fit_chunk && t.chunk > 64 && load < kMinPushWaves * t.chunk) t.chunk /= 2;
+        for (int s = 0; s < 2; ++s) {
+            const double n = (double)cfg[r].nx * (double)cfg[r].species[s].ppc;
+            load += n * std::max(1.0, cfg[r].capacity_factor / 4.0);
+            filled += cfg[r].geometry == SLPIC_GEOM_PLATES ? n / 8.0 : n;
+        }
+    const double push = sorts ? load / kMinPushWaves : filled / kMinLooseWaves;
+    while (fit_chunk && t.chunk > 64 && push < t.chunk) t.chunk /= 2;
     while (fit_tile && t.sort_tile >= 2 * kMinSortTile && load < kMinSortTiles * t.sort_tile) t.sort_tile /= 2;
 }
 

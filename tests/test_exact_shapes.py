@@ -70,6 +70,43 @@ def test_fitted_and_exact_shapes(gpu_lib):
         sim.close()
 
 
+# loads are 2 nx ppc particles: a sorting context halves chunks below 2048 of them,
+# one that does not below 256
+@pytest.mark.gpu
+@pytest.mark.parametrize("nx,ppc,prec,kw,chunk", [
+    (512, 255, "f32", {"chunk": 128}, 64), (512, 256, "f32", {"chunk": 128}, 128),
+    (1024, 511, "f64", {"chunk": 512}, 256), (1024, 512, "f64", {"chunk": 512}, 512),
+    (100, 1000, "f32", {}, 64), (100, 1000, "f32", {"sort_bucket": 256}, 64),
+    (100, 1000, "f32", {"sort_every": 0}, 512), (100, 1000, "f64", {"sort_every": 0}, 256),
+    (100, 1000, "f32", {"sort_bucket": 0}, 512), (100, 1000, "f32", {"sort_bucket": 257}, 512),
+    (512, 127, "f32", {"sort_every": 0}, 256), (512, 128, "f32", {"sort_every": 0}, 512),
+    (256, 63, "f64", {"sort_every": 0}, 64), (256, 64, "f64", {"sort_every": 0}, 128),
+])
+def test_fitted_chunk_steps_like_the_oracle(gpu_lib, nx, ppc, prec, kw, chunk):
+    print_case(f"fitted chunk {nx} x {ppc} {prec} {kw}")
+    cfg = workloads.sheath(nx, ppc, 4.0, seed=6, sort_every=0)
+    run = oracle.Run(cfg)
+    run.step(2)
+    sim = gpu_lib.Sim(cfg, precision=prec, **kw)
+    assert sim.launch_shape()[0] == chunk
+    push_oracle_to_gpu(sim, 0, run, quantize=prec == "f32")
+    sim.step(1)
+    run.step(1)
+    g, o = sim.grid(0), run.grid()
+    for s in range(2):  # the bounds of the other one-step comparisons
+        assert rel_inf(g["Q"][s], o["Q"][s]) <= {"f64": 1e-12, "f32": 1e-5}[prec], s
+    sim.close()
+
+
+@pytest.mark.gpu
+def test_fitted_chunk_of_unsorted_plates(gpu_lib):
+    """Counted by the eighth of its slots that the box fills."""
+    for ppc, want in ((500, 64), (2000, 128), (9000, 512)):
+        sim = gpu_lib.Sim(workloads.plates_sheath(0.0158, ppc=ppc), precision="f32", sort_every=0)
+        assert sim.launch_shape()[0] == want, ppc
+        sim.close()
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("u,chunk", [(2.0, 0), (10.0, 0), (math.inf, 0), (2.0, 64), (2.0, 128), (2.0, 256),
                                      (2.0, 1024)])
