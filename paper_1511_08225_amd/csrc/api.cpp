@@ -144,6 +144,8 @@ struct Plan {
     std::vector<int4> injb;  // plates: wall-injection workgroups (run, species, first particle, 0)
     int64_t total_slots = 0, total_nodes = 0, hist_entries = 0;
     int max_nodes = 0, max_src = 0, max_nkeys = 0;
+    int min_ppc = INT32_MAX;   // of every run and species
+    double fill = 1.0;         // the share of the slots that particles take (plates: when the box has filled)
     bool all_sheath = true;  // no plates or periodic run: the push without their paths
     bool all_step = true;    // every run takes Eq. (11b): the push without the smooth form
     bool any_varlim = false; // a run with a limit profile: the push that reads the profiles
@@ -220,6 +222,7 @@ int make_plan(const slpic_run_config* cfg, int nruns, const slpic_tuning* tin, P
     P.nruns = nruns;
     P.runs.assign(nruns, RunInfo{});
     int64_t poff = 0, goff = 0, hoff = 0;
+    double filled = 0.0;
     for (int r = 0; r < nruns; ++r) {
         const slpic_run_config& c = cfg[r];
         if (c.nx < 4 || c.nx > kMaxCells || !(c.dx > 0) || !(c.dt > 0) || !(c.u > 0) || c.nspecies != 2 ||
@@ -281,6 +284,7 @@ int make_plan(const slpic_run_config* cfg, int nruns, const slpic_tuning* tin, P
                 step_mixture(R.ut[s], R.Ps[s], R.Pf[s]);
             }
             R.ppc[s] = sp.ppc;
+            P.min_ppc = std::min(P.min_ppc, sp.ppc);
             R.nload[s] = plates ? 0 : (int64_t)c.nx * sp.ppc;  // plates: the box starts empty
             // plates: the one-sided flux v_t / sqrt(2 pi) of unit density, in g-particles per step
             R.wall_flux[s] = plates ? R.vt[s] / std::sqrt(2.0 * M_PI) * c.dt / R.w[s] : 0.0;
@@ -303,6 +307,7 @@ int make_plan(const slpic_run_config* cfg, int nruns, const slpic_tuning* tin, P
                 R.cap[s] = std::max<int64_t>((int64_t)std::ceil(cf * (double)nref), R.nload[s] + 64);
             }
             if (R.cap[s] > (int64_t(1) << 31) - 1) return SLPIC_EINVAL;
+            filled += plates ? (double)c.nx * sp.ppc / 8.0 : (double)R.nload[s];
             R.poff[s] = poff;
             poff += R.cap[s];
             R.ntiles[s] = (int32_t)((R.cap[s] + t.sort_tile - 1) / t.sort_tile);
@@ -328,6 +333,7 @@ int make_plan(const slpic_run_config* cfg, int nruns, const slpic_tuning* tin, P
     }
     if (poff > (int64_t(1) << 31) - 1) return SLPIC_EINVAL;  // sort offsets are int32
     P.total_slots = poff;
+    P.fill = std::min(1.0, filled / (double)poff);
     P.total_nodes = goff;
     P.hist_entries = hoff;
     P.run_chunk0.assign(nruns, 0);
@@ -513,16 +519,23 @@ int do_sort(Context* c, hipStream_t s) {
 }
 
 // The beta-weighted sums of nch chunks from ch0 added to out.  In cell order
-// means that a chunk's particles are within the 128 nodes of an LDS window: keys
-// of `bucket` cells, and particles that move less than two cells in a step
-// (sorted once, then unsorted steps, windows / whole rows: 4.1M particles 54 / 95
-// us after 32, 145 / 95 after 128; sorted by keys of 128 cells 43 / 38).
+// means that a chunk's particles are within an LDS window, which starts `below`
+// cells under the lowest cell of its first batch: keys of `bucket` cells, particles
+// that have moved a cell a step since the sort, and chunk / ppc cells of them.
+// Windows / whole rows in us, 4.1M particles: sorted once and 62 unsorted steps 45
+// / 81, 96 76 / 83, 200 187 / 83; keys of 32 cells 37 / 40, of 64 36 / 37, of 128 43
+// / 36.
 void l_moments(Context* c, int ch0, int nch, double* out, int per_run, int phi_runs, hipStream_t s) {
-    const bool ordered = c->P.tun.sort_bucket + 2 * c->moved <= 128;
-    if (prec(c) == SLPIC_F32)
-        launch_moments_f32(c->a, ch0, nch, c->P.tun.chunk, out, per_run, phi_runs, ordered, c->P.max_nodes, s);
-    else
-        launch_moments_f64(c->a, ch0, nch, c->P.tun.chunk, out, per_run, phi_runs, ordered, c->P.max_nodes, s);
+    MomentShape m;
+    const int chunk = c->P.tun.chunk;
+    m.below = (int)std::min<int64_t>(32, 8 + c->moved);
+    m.ordered = c->P.tun.sort_bucket + c->moved + m.below + chunk / c->P.min_ppc <= kWaveWindow;
+    m.max_nodes = c->P.max_nodes;
+    m.chunk = chunk;
+    m.cells_slots = 32 * (int64_t)c->P.min_ppc;
+    m.live = std::max(1, (int)(c->P.fill * nch));
+    if (prec(c) == SLPIC_F32) launch_moments_f32(c->a, ch0, nch, m, out, per_run, phi_runs, s);
+    else launch_moments_f64(c->a, ch0, nch, m, out, per_run, phi_runs, s);
 }
 
 // The moments of every run added to their device windows (slpic_moments_sample).

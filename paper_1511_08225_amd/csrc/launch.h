@@ -7,6 +7,16 @@
 
 namespace slpic {
 
+// What the moments launch goes by.
+struct MomentShape {
+    bool ordered;         // a chunk's particles lie within an LDS window
+    int below;            // cells that particles may have moved down since the sort
+    int max_nodes;        // of the longest run
+    int chunk;            // slots per chunk
+    int live;             // chunks, of those covered, that particles fill
+    int64_t cells_slots;  // slots of some tens of cells of the thinnest run
+};
+
 #define SLPIC_DECLARE_LAUNCHERS(sfx)                                                                   \
     void launch_load_##sfx(const KArgs& a, int nchunks, int block, hipStream_t s);                     \
     void launch_load_warm_##sfx(const KArgs& a, const void* cells, int ncells, hipStream_t s);         \
@@ -18,8 +28,8 @@ namespace slpic {
     void launch_source_field_##sfx(const KArgs& a, int nruns, int threads, size_t lds, hipStream_t s); \
     void launch_wall_inject_##sfx(const KArgs& a, hipStream_t s);                                      \
     void launch_limit_##sfx(const KArgs& a, const LimitArgs& L, int nchunks, int scatter, hipStream_t s); \
-    void launch_moments_##sfx(const KArgs& a, int chunk0, int nchunks, int chunk, double* out,         \
-                              int per_run, int phi_runs, bool ordered, int max_nodes, hipStream_t s);                               \
+    void launch_moments_##sfx(const KArgs& a, int chunk0, int nchunks, const MomentShape& m,           \
+                              double* out, int per_run, int phi_runs, hipStream_t s);                               \
     void launch_sort_hist_##sfx(const KArgs& a, int ntiles, int block, size_t lds, int whole,          \
                                 hipStream_t s);                                                        \
     void launch_sort_scatter_##sfx(const KArgs& a, int ntiles, int block, size_t lds, hipStream_t s);
