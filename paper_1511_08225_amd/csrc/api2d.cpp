@@ -266,10 +266,10 @@ int timed2(Ctx2* c, int k, hipStream_t s, F&& f) {
 int push2(Ctx2* c, bool push, hipStream_t s) {
     const Plan2& P = c->P;
     int rc = 0;
-    if (f32(c)) rc = launch2d_push_f32(push, P.tun.per_thread, c->a, P.R.nkeys, P.push_lparts, P.tun.tail_groups,
+    const int lparts = c->sorted ? P.push_lparts : -1;  // no sort since the load or an import: no tiles
+    if (f32(c)) rc = launch2d_push_f32(push, P.tun.per_thread, c->a, P.R.nkeys, lparts, P.tun.tail_groups,
                                        P.push_lds, s);
-    else rc = launch2d_push_f64(push, P.tun.per_thread, c->a, P.R.nkeys, P.push_lparts, P.tun.tail_groups,
-                                P.push_lds, s);
+    else rc = launch2d_push_f64(push, P.tun.per_thread, c->a, P.R.nkeys, lparts, P.tun.tail_groups, P.push_lds, s);
     return rc ? SLPIC_EINVAL : SLPIC_OK;
 }
 
