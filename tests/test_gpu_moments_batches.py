@@ -103,3 +103,45 @@ def test_cells_below_the_first_batch(gpu_lib):
             sim.import_particles(0, s, *parts[s])
         _check(sim, cfg, parts)
     sim.close()
+
+
+@pytest.mark.parametrize("prec,beta", [("f32", "step"), ("f64", "smooth")])
+@pytest.mark.parametrize("nx,ppc,chunk", [
+    (100, 40, 512),    # fits the window
+    (127, 40, 256),    # 128 and 129 nodes: about the window's
+    (128, 40, 1024),
+    (150, 30, 64),
+    (300, 60, 1024),
+    (2729, 9, 512),
+])
+def test_windows_across_the_ends_of_a_box(gpu_lib, prec, beta, nx, ppc, chunk):
+    """Particles that crossed the ends since the sort lie in chunks of the other
+    end; nodes 0 and nx each keep their own sums."""
+    print_case(f"moments of a box {nx} x {ppc} chunk={chunk} {prec} {beta}")
+    cfg = workloads.langmuir_box(1.0, nx=nx, ppc=ppc, seed=nx, beta_kind=beta)
+    sim = gpu_lib.Sim(cfg, precision=prec, sort_every=16, chunk=chunk | gpu_lib.EXACT)
+    for steps in (0, 1, 4, 10, 1):
+        sim.step(steps)
+        _check(sim, cfg, [sim.export_particles(0, s) for s in range(2)])
+    sim.close()
+
+
+def test_windows_of_boxes_and_sheaths_share_a_launch(gpu_lib):
+    cfgs = [dict(workloads.langmuir_box(1.0, nx=200, ppc=30, seed=1), run=0),
+            dict(workloads.sheath(300, 20, 4.0, seed=2), run=1),
+            dict(workloads.langmuir_box(0.5, nx=90, ppc=20, seed=3), run=2),
+            dict(workloads.plates_sheath(0.0158, ppc=300, seed=4), run=3)]
+    print_case("moments of boxes, sheaths and plates in one launch")
+    sim = gpu_lib.Sim(cfgs, precision="f64", sort_every=8, chunk=256 | gpu_lib.EXACT)
+    for steps in (1, 12):
+        sim.step(steps)
+        sim.moments_sample(-1)
+        st = sim.status()
+        for r, cfg in enumerate(cfgs):
+            win = sim.moments_window(r, reset=True).cpu().numpy()
+            for s in range(2):
+                want = _rows(cfg, st[r]["weight"], *sim.export_particles(r, s), s)
+                for k in range(3):
+                    if np.abs(want[k]).max() > 0:
+                        assert rel_inf(win[1 + 3 * s + k], want[k]) <= TOL, (r, s, k)
+    sim.close()
